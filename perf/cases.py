@@ -137,15 +137,18 @@ class Inputs:
         return self.qkv[t % len(self.qkv)], self.windows[t % len(self.windows)]
 
 
+def _smoothing(case):
+    """(alpha, rows, columns, special tokens, 3x3 kernel) of Eq. 6, or None."""
+    if not case["smooth"]:
+        return None
+    grid = synth.StreamConfig("", case["M"], case["H"], HEAD_DIM, case["C"], case["B"], 1, 1, case["dtype"], SPECIAL, "", "")
+    ph, pw = synth.patch_grid(grid)
+    return 0.5, ph, pw, SPECIAL, synth.gaussian_kernel3(1.0)
+
+
 def _make_cache(case):
-    M = case["M"]
-    smooth = None
-    if case["smooth"]:
-        grid = synth.StreamConfig("", M, case["H"], HEAD_DIM, case["C"], case["B"], 1, 1, case["dtype"], SPECIAL, "", "")
-        ph, pw = synth.patch_grid(grid)
-        smooth = (0.5, ph, pw, SPECIAL, synth.gaussian_kernel3(1.0))
-    return B.Cache(case["layers"], case["H"], HEAD_DIM, M, case["C"], case["B"], case["dtype"], out_dtype=case["out"],
-                   smooth=smooth, hybrid_beta=0.5 if case["hybrid"] else None)
+    return B.Cache(case["layers"], case["H"], HEAD_DIM, case["M"], case["C"], case["B"], case["dtype"], out_dtype=case["out"],
+                   smooth=_smoothing(case), hybrid_beta=0.5 if case["hybrid"] else None)
 
 
 def _anchors(case, t):
@@ -269,3 +272,115 @@ def tolerance(case):
     if case["out"] == "bf16":
         return {"rel": 7e-3, "max": 2e-2}
     return {"rel": 1.2e-3, "max": 1e-2}
+
+
+# ---- the same passes in plain torch: attention in 64 bits, on the tokens that Eq. 8 keeps ------------
+# Which tokens those are hangs on the last bit of a score, so scores follow the sequence that defines
+# them: single fp32 operations, sums as balanced trees over neighbours.
+
+def _tree(x):
+    """Row sums of [n, w] as a balanced binary tree over neighbours, zero-padded to a power of two."""
+    x = torch.nn.functional.pad(x, (0, (1 << (x.shape[1] - 1).bit_length()) - x.shape[1]))
+    while x.shape[1] > 1:
+        x = x[:, 0::2] + x[:, 1::2]
+    return x[:, 0]
+
+
+def _sqrt(x):
+    return x.double().sqrt().float()                # correctly rounded
+
+
+def _div(x, y):
+    return (x.double() / y.double()).float()        # correctly rounded
+
+
+def _min_max(x, weight):
+    lo, hi = x.min(), x.max()
+    unit = torch.zeros_like(x) if bool(lo == hi) else _div(x - lo, hi - lo)
+    return weight * unit
+
+
+class ExactLayer:
+    """One layer's cache in the order of arrival: keys, values, rank keys and protection of the resident tokens."""
+
+    def __init__(self, case):
+        self.case, self.smooth = case, _smoothing(case)
+        self.k = self.v = torch.zeros((0, case["H"], HEAD_DIM), dtype=TYPES[case["dtype"]], device="cuda")
+        self.key = torch.zeros(0, device="cuda")
+        self.kept = torch.zeros(0, dtype=torch.bool, device="cuda")
+
+    def append(self, k, v):
+        self.k, self.v = torch.cat([self.k, k]), torch.cat([self.v, v])
+
+    def attend(self, q):
+        out = torch.empty(q.shape, dtype=torch.float64, device="cuda")
+        for h in range(q.shape[1]):
+            s = torch.mm(q[:, h].double(), self.k[:, h].double().t().contiguous()) / math.sqrt(HEAD_DIM)
+            out[:, h] = torch.mm(torch.softmax(s, dim=1), self.v[:, h].double())
+        return out
+
+    def close(self, r, anchors):
+        """Scores of the frame just appended, then the budget."""
+        r = r.float()
+        key = _tree(r * r)
+        if self.smooth is not None:
+            alpha, ph, pw, first, g = self.smooth
+            key = _sqrt(key)
+            grid = torch.nn.functional.pad(key[first:].view(1, 1, ph, pw), (1, 1, 1, 1), mode="replicate")[0, 0]
+            conv = None
+            for t in range(9):
+                prod = float(g[t // 3, t % 3]) * grid[t // 3:t // 3 + ph, t % 3:t % 3 + pw]
+                conv = prod if conv is None else conv + prod
+            key[first:] = alpha * conv.reshape(-1) + (1.0 - alpha) * key[first:]
+        n_old = len(self.key)
+        self.key = torch.cat([self.key, key])
+        new = torch.zeros(len(key), dtype=torch.bool, device="cuda") if anchors is None else anchors.bool()
+        self.kept = torch.cat([self.kept, new])
+        budget = self.case["B"]
+        if len(self.key) <= budget:
+            return
+        free = torch.nonzero(~self.kept)[:, 0]
+        if self.case["hybrid"]:
+            self._rank_by_diversity(free[free < n_old], free[free >= n_old])
+        best = torch.sort(self.key[free], descending=True, stable=True).indices[:budget - int(self.kept.sum())]
+        stay = torch.sort(torch.cat([torch.nonzero(self.kept)[:, 0], free[best]])).values
+        self.k, self.v, self.key, self.kept = self.k[stay], self.v[stay], self.key[stay], self.kept[stay]
+
+    def _rank_by_diversity(self, hist, new):
+        """Eq. 7: min-max of 1 - cos(key, centroid) for the history, of the scores for the new frame."""
+        if len(hist):
+            k = self.k[hist].half().float().reshape(len(hist), -1)
+            total = torch.zeros(k.shape[1], dtype=torch.int64, device="cuda")
+            for part in k.split(4096):
+                total += (part.double() * 2.0 ** 24).long().sum(0)
+            c = (total.double().float() * 2.0 ** -24)[None]
+            den = _sqrt(_tree(k * k)) * _sqrt(_tree(c * c))
+            cos = torch.where(den == 0, 0.0, _div(_tree(k * c), den))
+            self.key[hist] = _min_max(1.0 - cos, 0.5)
+        if len(new):
+            s = self.key[new]
+            self.key[new] = _min_max(s if self.smooth is not None else _sqrt(s), 0.5)
+
+
+def exact(case, seed):
+    """The first pass on these inputs; ids, flags, scores and the exported rows are compared as they are."""
+    inputs = Inputs(case, seed)
+    layers = [ExactLayer(case) for _ in range(case["layers"])]
+
+    def frame(anchors, attend, close=True):
+        (q, k, v), r = inputs.next()
+        outs = []
+        for l, x in enumerate(layers):
+            x.append(k[l], v[l])
+            if attend:
+                outs.append(x.attend(q[l]))
+            if close:
+                x.close(r[l], None if anchors is None else anchors[l])
+        return torch.stack(outs) if attend else None
+
+    if case["kind"] == "clip":
+        return [frame(_anchors(case, t), True) for t in range(case["frames"])]
+    for t in range(-(-case["B"] // case["M"]) + 1):
+        frame(_anchors(case, t), False)
+    out = frame(None, True, close=False)
+    return [out, None, None, None, None, None] if case["kind"] == "checkpoint" else out
