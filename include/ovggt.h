@@ -131,7 +131,7 @@ int ovggt_cache_init(ovggt_cache** out, const ovggt_config* cfg,
  * Q K^T and P V on the f16 MFMA with fp32 accumulation (K and V are cached as IEEE
  * half, the queries are multiplied by scale*log2(e) and rounded to half, softmax
  * weights are rounded to half) and an fp32 online softmax; f32 runs compute in
- * fp32.  Accuracy of bf16 runs: the rounded query makes a logit of magnitude x
+ * fp32 (f32 MFMA, fp32 softmax).  Accuracy of bf16 runs: the rounded query makes a logit of magnitude x
  * (after the scale, in units of ln 2) uncertain by about x * 2^-12, so the
  * output error relative to the output's RMS is a few 1e-3 for logits of unit
  * spread and approaches 2e-2 when their spread reaches 16.  Range of bf16 runs: K
@@ -154,7 +154,7 @@ int ovggt_global_attn(ovggt_cache* c, int layer, const void* q, const void* k_ne
  * n_heads) whose heads cannot be handed out as whole (head pair, query block) items -- the head
  * pairs do not divide among the chip's 8 XCDs, or there are fewer items than workgroups -- needs
  * more records than the array holds, returns OVGGT_ERR_TOO_LARGE and changes nothing; f32 handles
- * use no workspace and behave as ovggt_global_attn.  Every call on a GPU shares that GPU's array: calls that may overlap
+ * keep to the workspace given to ovggt_cache_init and behave as ovggt_global_attn.  Every call on a GPU shares that GPU's array: calls that may overlap
  * on one GPU (different streams, different handles) race and must be ordered by the caller. */
 int ovggt_global_attn_static_ws(ovggt_cache* c, int layer, const void* q, const void* k_new, const void* v_new,
                                 void* out, void* hip_stream);

@@ -1,77 +1,273 @@
 // fp32 attention of the new frame's queries over the resident cache (paper
-// Sec. 3.1), for handles whose dtype is f32.  This is the accuracy path of the
-// small all-fp32 workload (tolerance 1e-4 of output RMS), not a tuned kernel:
-// one workgroup per (query, head), two passes over the keys (row maximum, then
-// exp / sum / weighted values), everything accumulated in fp32.
+// Sec. 3.1), for handles whose dtype is f32.
+//
+// Everything stays in fp32: both products run on v_mfma_f32_16x16x4_f32, the
+// softmax between them on the VALU.
+//   S^T = K Q^T      A = K rows, B = Q^T; a lane holds one query's scores
+//   O^T = V^T P^T    A = V^T, B = P^T straight from the S^T accumulators
+// The order in which a contraction index is walked is free, so operands are
+// taken from memory the way they lie there: of a 16-slot tile lane (l16, g)
+// reads 16-byte pieces of K row l16 (elements 16 j + 4 g .. +3) and of V rows
+// 4 g .. 4 g + 3 (elements 4 l16 .. +3), whole 64- and 256-byte runs, and both
+// enter the matrix unit from these registers; no operand passes through LDS.
+//
+// 1041 queries over 5137 slots, 16 heads (22 GFLOP): 39.5 ms as a scalar kernel with
+// one workgroup per query, 225 us like this, 97 TFLOP/s; the f32 matrix rate (157
+// at 2.4 GHz) bounds it: the matrix pipes are busy 60 % of the time, and what they
+// wait for is K and V out of L2 (11 TB/s: a 16-query block re-reads both).  Blocks of
+// 32 queries halve that traffic but fill the chip worse (528 instead of 1056 blocks
+// for 256 CUs) and took 10 to 20 % longer over every size from 17 to 1041 queries.
 #include "ovggt_internal.h"
 
 namespace ovggt {
 
-constexpr int kF32Threads = 256;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
 
-__device__ inline float block_reduce_max(float v, float* tmp) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v = fmaxf(v, __shfl_xor(v, off, 64));
-  if ((threadIdx.x & 63) == 0) tmp[threadIdx.x >> 6] = v;
-  __syncthreads();
-  float r = tmp[0];
-  for (int w = 1; w < kF32Threads / 64; ++w) r = fmaxf(r, tmp[w]);
-  __syncthreads();
-  return r;
+constexpr float kF32Lag = 8.0f;         // the softmax reference may lag the running maximum by 2^8
+constexpr int kF32Rows = 16;            // queries of a workgroup
+constexpr int kF32Waves = 8;
+constexpr int kF32Threads = 64 * kF32Waves;
+constexpr int kF32Pitch = 68;           // floats per row of the merge area (64 + 4: rows start on different banks)
+constexpr int kF32RecFloats = kF32Rows * 64 + 2 * kF32Rows;      // one part's O rows, then references and weight sums
+constexpr int kF32MaxSplits = 16;
+constexpr int kF32MaxRecs = 4096;       // parts of a split launch (17 MB of workspace at most)
+
+// Workspace of an fp32 handle: an arrival counter per query block, then one record per part.
+static size_t f32_counter_bytes() { return (size_t)kF32MaxRecs / 2 * sizeof(uint32_t); }
+size_t attn_f32_ws_bytes(int layer_heads, int tokens_per_frame) {
+  const long blocks = (long)((tokens_per_frame + kF32Rows - 1) / kF32Rows) * layer_heads;
+  const long recs = blocks * kF32MaxSplits < kF32MaxRecs ? blocks * kF32MaxSplits : kF32MaxRecs;
+  return f32_counter_bytes() + (size_t)recs * kF32RecFloats * sizeof(float);
 }
 
+struct AttnF32Params {
+  const char* kv;
+  const float* q;
+  float* out;
+  uint32_t* arrive;           // one counter per query block, zero between launches
+  float* recs;
+  int layer0, n_total, QB, n_work, splits;
+  float c;                    // softmax scale * log2(e)
+};
+
+__device__ inline void store_through(float* p, const f32x4& v) {
+  const float2 a = {v[0], v[1]}, b = {v[2], v[3]};
+  __hip_atomic_store((unsigned long long*)p, __builtin_bit_cast(unsigned long long, a), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __hip_atomic_store((unsigned long long*)p + 1, __builtin_bit_cast(unsigned long long, b), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// A workgroup takes 16 queries of one head over one of `splits` equal ranges of
+// the slots; its waves share the 16-slot tiles of the range (wave w: every 8th
+// from the w-th) and merge through LDS.  With more than one range, the parts go
+// to memory and the workgroup that arrives last for a query block merges them.
 __global__ void __launch_bounds__(kF32Threads)
-attn_f32_kernel(Geom g, char* kv, int layer0, const float* q, float* out, int n_total, float scale) {
-  __shared__ float qs[64];
-  __shared__ float tmp[kF32Threads / 64];
-  __shared__ float acc[kF32Threads / 64][65];
-  const int m = blockIdx.x, h = blockIdx.y, li = blockIdx.z;
-  const int layer = layer0 + li;
-  const int tid = threadIdx.x;
-  const float* kbase = (const float*)layer_k(kv, g, layer) + (size_t)h * g.cap * 64;
-  const float* vbase = (const float*)layer_v(kv, g, layer) + (size_t)h * g.cap * 64;
-  const size_t qoff = (((size_t)li * g.M + m) * g.H + h) * 64;
-  if (tid < 64) qs[tid] = q[qoff + tid];
-  __syncthreads();
+attn_f32_kernel(Geom g, AttnF32Params p) {
+  constexpr int W = kF32Waves;
+  __shared__ float mO[W][kF32Rows][kF32Pitch];
+  __shared__ float mM[W][kF32Rows], mL[W][kF32Rows];
+  __shared__ uint32_t is_last;
+  // Consecutive workgroups of an XCD walk the query blocks of one range of one head, whose K and V
+  // rows then come from that XCD's L2.
+  const int idx = (int)(blockIdx.x & 7) * (int)(gridDim.x >> 3) + (int)(blockIdx.x >> 3);
+  if (idx >= p.n_work) return;                                       // whole workgroup
+  const int qb = idx % p.QB, rest = idx / p.QB;
+  const int sp = rest % p.splits, lh = rest / p.splits;
+  const int q0 = qb * kF32Rows;
+  const int li = lh / g.H, h = lh - li * g.H;
+  const int lane = threadIdx.x & 63, l16 = lane & 15, gl = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const float* kbase = (const float*)layer_k((char*)p.kv, g, p.layer0 + li) + (size_t)h * g.cap * 64;
+  const float* vbase = (const float*)layer_v((char*)p.kv, g, p.layer0 + li) + (size_t)h * g.cap * 64;
 
-  // pass 1: maximum logit
-  float mx = -INFINITY;
-  for (int j = tid; j < n_total; j += kF32Threads) {
-    const float* kr = kbase + (size_t)j * 64;
-    float s = 0.f;
-#pragma unroll 16
-    for (int e = 0; e < 64; ++e) s = fmaf(qs[e], kr[e], s);
-    mx = fmaxf(mx, s * scale);
+  f32x4 qf[4];
+  {
+    const float* qp = p.q + (((size_t)li * g.M + min(q0 + l16, g.M - 1)) * g.H + h) * 64 + 4 * gl;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) qf[j] = *(const f32x4*)(qp + 16 * j);
   }
-  mx = block_reduce_max(mx, tmp);
+  const int n_total = p.n_total, nt = (n_total + 15) >> 4;
+  const int t0 = (int)((long)nt * sp / p.splits), t1 = (int)((long)nt * (sp + 1) / p.splits);
+  const bool ragged = (n_total & 15) != 0;
+  const float c = p.c;
+  f32x4 kf[4], vf[4], O[4];
+  float m = -3.402823466e38f, l = 0.f;
+#pragma unroll
+  for (int d = 0; d < 4; ++d) O[d] = f32x4{0.f, 0.f, 0.f, 0.f};
+  // rows at or beyond n_total are never read (they may hold anything): the last resident row stands in
+  auto load_k = [&](int t) {
+    const float* kp = kbase + (size_t)min(t * 16 + l16, n_total - 1) * 64 + 4 * gl;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) kf[j] = *(const f32x4*)(kp + 16 * j);
+  };
+  auto load_v = [&](int t) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      vf[i] = *(const f32x4*)(vbase + (size_t)min(t * 16 + 4 * gl + i, n_total - 1) * 64 + 4 * l16);
+  };
+  if (t0 + wave < t1) { load_k(t0 + wave); load_v(t0 + wave); }
+  for (int t = t0 + wave; t < t1; t += W) {
+    const int tn = min(t + W, t1 - 1);
+    f32x4 S;
+    {
+      f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0;        // two chains: a product never waits for the one before it
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int j = 0; j < 4; j += 2) {
+          s0 = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[j][e], qf[j][e], s0, 0, 0, 0);
+          s1 = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[j + 1][e], qf[j + 1][e], s1, 0, 0, 0);
+        }
+      S = s0 + s1;
+    }
+    load_k(tn);                                        // K of the next tile travels during this tile's P V, V during its Q K
+    if (ragged && t == nt - 1) {                       // absent slots: no weight, and no 0 * inf from the stand-in row
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const bool absent = t * 16 + 4 * gl + i >= n_total;
+        S[i] = absent ? -INFINITY : S[i];
+        if (absent) vf[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+      }
+    }
+    // The reference m follows the maximum only when it is passed by 2^8 (weights are fp32: no
+    // accuracy is lost), so most tiles rescale nothing and look at no other lane.
+    const float mx = fmaxf(fmaxf(S[0], S[1]), fmaxf(S[2], S[3])) * c;
+    if (__builtin_amdgcn_ballot_w64(mx > m + kF32Lag) != 0ull) {
+      float x = fmaxf(mx, __shfl_xor(mx, 16, 64));
+      x = fmaxf(x, __shfl_xor(x, 32, 64));
+      const float mn = fmaxf(m, x), a = __builtin_amdgcn_exp2f(m - mn);
+      m = mn;
+      l *= a;
+#pragma unroll
+      for (int d = 0; d < 4; ++d) O[d] *= a;
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) S[i] = __builtin_amdgcn_exp2f(fmaf(S[i], c, -m));
+    l += (S[0] + S[1]) + (S[2] + S[3]);
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int d = 0; d < 4; ++d) O[d] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[i][d], S[i], O[d], 0, 0, 0);
+    load_v(tn);
+  }
 
-  // pass 2: thread t owns output element e = t & 63 and every 4th key
-  const int e = tid & 63, grp = tid >> 6;
-  float l = 0.f, o = 0.f;
-  for (int j = grp; j < n_total; j += kF32Threads / 64) {
-    const float* kr = kbase + (size_t)j * 64;
-    float s = 0.f;
-#pragma unroll 16
-    for (int c = 0; c < 64; ++c) s = fmaf(qs[c], kr[c], s);
-    const float p = __expf(s * scale - mx);
-    l += p;
-    o = fmaf(p, vbase[(size_t)j * 64 + e], o);
-  }
-  acc[grp][e] = o;
-  if (e == 0) acc[grp][64] = l;
+  // ---- merge of the waves: the common reference first, then the rescaled parts
+  l += __shfl_xor(l, 16, 64);
+  l += __shfl_xor(l, 32, 64);
+  if (gl == 0) { mM[wave][l16] = m; mL[wave][l16] = l; }
   __syncthreads();
-  if (tid < 64) {
-    float os = 0.f, ls = 0.f;
-    for (int w = 0; w < kF32Threads / 64; ++w) { os += acc[w][tid]; ls += acc[w][64]; }
-    out[qoff + tid] = os / ls;
+  {
+    float mt = mM[0][l16];
+#pragma unroll
+    for (int w = 1; w < W; ++w) mt = fmaxf(mt, mM[w][l16]);
+    const float a = __builtin_amdgcn_exp2f(m - mt);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const f32x4 o = {O[0][i] * a, O[1][i] * a, O[2][i] * a, O[3][i] * a};
+      *(f32x4*)&mO[wave][l16][16 * gl + 4 * i] = o;
+    }
   }
+  __syncthreads();
+  const int row = (int)threadIdx.x >> 4, piece = (int)threadIdx.x & 15;      // the first four waves: 16 rows of 16 pieces
+  f32x4 o = {0.f, 0.f, 0.f, 0.f};
+  float ls = 0.f, mt = 0.f;
+  if (row < kF32Rows) {
+    mt = mM[0][row];
+#pragma unroll
+    for (int w = 1; w < W; ++w) mt = fmaxf(mt, mM[w][row]);
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+      ls += mL[w][row] * __builtin_amdgcn_exp2f(mM[w][row] - mt);
+      o += *(const f32x4*)&mO[w][row][4 * piece];
+    }
+  }
+  if (p.splits > 1) {
+    // Parts are written through to device-coherent memory, so a wave waits for its own stores only;
+    // the counter is a relaxed device-scope atomic and the last arrival invalidates its caches.
+    const size_t first = ((size_t)lh * p.splits) * p.QB + qb;        // record of range 0; the ranges are QB apart
+    if (row < kF32Rows) {
+      float* rec = p.recs + (first + (size_t)sp * p.QB) * kF32RecFloats;
+      store_through(rec + row * 64 + 4 * piece, o);
+      if (piece == 0) {
+        __hip_atomic_store(rec + kF32Rows * 64 + row, mt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(rec + kF32Rows * 65 + row, ls, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      uint32_t* cnt = p.arrive + (size_t)lh * p.QB + qb;
+      const bool last = __hip_atomic_fetch_add(cnt, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)p.splits - 1u;
+      if (last) {
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        __hip_atomic_store(cnt, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+      is_last = last ? 1u : 0u;
+    }
+    __syncthreads();
+    if (!is_last || row >= kF32Rows) return;
+    float pm[kF32MaxSplits];
+    mt = -INFINITY;
+#pragma unroll
+    for (int s = 0; s < kF32MaxSplits; ++s) {          // ranges beyond the last repeat it, with no weight
+      pm[s] = p.recs[(first + (size_t)min(s, p.splits - 1) * p.QB) * kF32RecFloats + kF32Rows * 64 + row];
+      mt = fmaxf(mt, pm[s]);
+    }
+    o = f32x4{0.f, 0.f, 0.f, 0.f};
+    ls = 0.f;
+#pragma unroll 4
+    for (int s = 0; s < p.splits; ++s) {
+      const float* rec = p.recs + (first + (size_t)s * p.QB) * kF32RecFloats;
+      const float a = __builtin_amdgcn_exp2f(rec[kF32Rows * 64 + row] - mt);
+      ls += rec[kF32Rows * 65 + row] * a;
+      o += *(const f32x4*)(rec + row * 64 + 4 * piece) * a;
+    }
+  }
+  if (row < kF32Rows && q0 + row < g.M) {
+    const f32x4 r = {o[0] / ls, o[1] / ls, o[2] / ls, o[3] / ls};
+    *(f32x4*)(p.out + (((size_t)li * g.M + q0 + row) * g.H + h) * 64 + 4 * piece) = r;
+  }
+}
+
+// Ranges per query block.  Fewer blocks than CUs: one range more for every CU that would idle, as long
+// as a range keeps 16 tiles, two for each wave (step time, 65 queries of 2 heads over 4161 slots: 60 us
+// with 1 range, 33 with 4, 29 with 16; 700 queries of one head over 4796: 68 with 1, 36 with 4, 41 with 6;
+// 17 of 8 heads over 1017: 28 with 1, 24 with 4).  More blocks than CUs: ranges smooth the last,
+// partly filled round (1056 blocks = 4.1 a CU: 286 us with 1 range, 259 with 2, 250 with 3 and with 16).
+static int f32_splits(long blocks, int n_tiles, long max_recs) {
+  constexpr long kCus = 256;
+  long s = 1;
+  if (blocks < kCus) {
+    s = kCus / blocks;
+    if (s > n_tiles / 16) s = n_tiles / 16;
+    if (s > kF32MaxSplits) s = kF32MaxSplits;
+  } else if (blocks <= kF32MaxRecs / 2) {
+    float best = 0.f;
+    for (long k = 1; k <= 4 && n_tiles / k >= 64; ++k) {
+      const long rounds = (blocks * k + kCus - 1) / kCus;
+      const float full = (float)(blocks * k) / (float)(rounds * kCus);
+      if (full > best + 0.02f) { best = full; s = k; }
+    }
+  }
+  while (s > 1 && blocks * s > max_recs) --s;
+  return s < 1 ? 1 : (int)s;
 }
 
 hipError_t launch_attn_f32(const Geom& g, char* kv, int layer0, int nl, const void* q, void* out,
-                           int n_total, float scale, hipStream_t s) {
-  dim3 grid((unsigned)g.M, (unsigned)g.H, (unsigned)nl);
-  hipLaunchKernelGGL(attn_f32_kernel, grid, dim3(kF32Threads), 0, s, g, kv, layer0,
-                     (const float*)q, (float*)out, n_total, scale);
+                           int n_total, float scale, char* ws, size_t ws_bytes, hipStream_t s) {
+  AttnF32Params p;
+  p.kv = kv; p.q = (const float*)q; p.out = (float*)out;
+  p.arrive = (uint32_t*)ws;
+  p.recs = (float*)(ws + f32_counter_bytes());
+  p.layer0 = layer0; p.n_total = n_total;
+  p.QB = (g.M + kF32Rows - 1) / kF32Rows;
+  p.c = scale * 1.4426950408889634f;
+  const long blocks = (long)p.QB * g.H * nl;
+  const long max_recs = ws_bytes > f32_counter_bytes() ? (long)((ws_bytes - f32_counter_bytes()) / (kF32RecFloats * sizeof(float))) : 0;
+  p.splits = f32_splits(blocks, (n_total + 15) / 16, max_recs);
+  const long work = blocks * p.splits;
+  if (work > 0x7FFFFFF0L) return hipErrorInvalidValue;
+  p.n_work = (int)work;
+  hipLaunchKernelGGL(attn_f32_kernel, dim3((unsigned)((work + 7) / 8 * 8)), dim3(kF32Threads), 0, s, g, p);
   return hipGetLastError();
 }
 

@@ -130,7 +130,7 @@ int query_blocks(const ovggt_config& c) { return (c.tokens_per_frame + kQueryTil
 
 // the larger of what a single-layer launch and an all-layers launch need
 size_t ws_bytes_for(const ovggt_config& c) {
-  if (c.dtype != OVGGT_BF16) return 256;
+  if (c.dtype != OVGGT_BF16) return up256(attn_f32_ws_bytes(c.n_layers * c.n_heads, c.tokens_per_frame));
   const size_t one = attn_ws_bytes(c.n_heads, query_blocks(c)), all = attn_ws_bytes(c.n_layers * c.n_heads, query_blocks(c));
   return up256(one > all ? one : all);
 }
@@ -312,7 +312,7 @@ static int global_attn_impl(ovggt_cache* c, int layer, const void* q, const void
     }
   } else {
     ProfScope ps(c, OVGGT_PROF_ATTN, s, prof_attn);
-    e = launch_attn_f32(g, c->kv, l0, nl, q, out, n + g.M, c->scale, s);
+    e = launch_attn_f32(g, c->kv, l0, nl, q, out, n + g.M, c->scale, ws, ws_bytes, s);
   }
   if (e != hipSuccess) return OVGGT_ERR_HIP;
   for (int l = l0; l < l0 + nl; ++l) { c->n[l] = n + g.M; c->phase[l] = 1; }

@@ -78,7 +78,8 @@ hipError_t launch_append(const Geom& g, char* kv, char* meta, int layer0, int nl
 
 // Attention of M queries over n_total resident slots.
 hipError_t launch_attn_f32(const Geom& g, char* kv, int layer0, int nl, const void* q, void* out,
-                           int n_total, float scale, hipStream_t s);
+                           int n_total, float scale, char* ws, size_t ws_bytes, hipStream_t s);
+size_t attn_f32_ws_bytes(int layer_heads, int tokens_per_frame);
 // `ev` (optional, 3 events) are recorded before the main kernel, between it and
 // the combine kernel, and after the combine kernel.
 hipError_t launch_attn_bf16(const Geom& g, char* kv, int layer0, int nl, const void* q, void* out,

@@ -1,0 +1,66 @@
+"""fp32 attention against fp64 softmax over the same rows, at the edges of its tiles: 16 queries to a
+workgroup, 16 slots to a tile, eight waves and up to 16 slot ranges that share the tiles."""
+import numpy as np
+import pytest
+
+from paper_2603_05959_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("M,n_old,H,layers", [
+    (1, 1, 1, 1), (1, 14, 3, 1), (1, 16, 1, 2),        # one tile, its last slot absent, one slot of the next
+    (15, 113, 2, 1), (16, 112, 2, 1), (17, 112, 2, 2),  # eight tiles: one a wave; one query of the next block
+    (2, 254, 1, 1), (3, 254, 1, 1), (33, 1000, 1, 1),   # from where the slots are split into ranges
+    (16, 4080, 1, 1), (40, 4057, 3, 2),                 # the most ranges; ranges of unequal length
+    (272, 1300, 16, 1), (97, 2048, 4, 24),              # more blocks than CUs: two or more ranges each, and one
+])
+def test_matches_fp64_softmax(M, n_old, H, layers):
+    import torch
+    gen = torch.Generator().manual_seed(M * 1000 + n_old)
+    cache = B.Cache(layers, H, 64, M, 64, max(n_old, M), "f32")
+    n_old = min(n_old, max(n_old, M))
+    rnd = lambda *s: torch.randn(s, generator=gen, dtype=torch.float32)
+    old = [(rnd(n_old, H, 64), rnd(n_old, H, 64)) for _ in range(layers)]
+    # three frames seen, so that a later frame's ids stay unique
+    for l, (k, v) in enumerate(old):
+        cache.import_(l, 3 + n_old // M, np.arange(n_old, dtype=np.uint32), k.numpy(), v.numpy(),
+                      np.ones(n_old, np.float32), np.zeros(n_old, np.uint8))
+    out = cache.new_output()
+    for rep in range(2):                                # the arrival counters are back at zero for the second frame
+        q, k, v = (rnd(layers, M, H, 64) for _ in range(3))
+        q[:, 0] *= 12.0                                 # one dominant key, and a reference that is passed by far
+        cache.step(q.cuda(), k.cuda(), v.cuda(), torch.ones(layers, M, 64, device="cuda"), None, out)
+        got = out.cpu().double()
+        for l in range(layers):
+            kk, vv = torch.cat([old[l][0], k[l]]).double(), torch.cat([old[l][1], v[l]]).double()
+            p = torch.softmax(torch.einsum("mhd,nhd->hmn", q[l].double(), kk) / 8.0, dim=-1)
+            ref = torch.einsum("hmn,nhd->mhd", p, vv)
+            # a score carries at most about 64 roundings of 2^-24 times its terms' size (|s| up to about 60 in the
+            # scaled rows): relative errors of weights and outputs near 1e-5 at worst, 1e-6 in the mean
+            assert (got[l] - ref).norm() / ref.norm() < 5e-6, (rep, l)
+        e = [cache.export(l) for l in range(layers)]
+        old = [(torch.from_numpy(x["k"]), torch.from_numpy(x["v"])) for x in e]
+    cache.close()
+
+
+def test_rows_behind_the_last_slot_are_not_read():
+    """Evicted entries stay in memory behind the resident ones, infinities and NaN among them."""
+    import torch
+    M, H, Bq = 5, 2, 19
+    gen = torch.Generator().manual_seed(2)
+    cache = B.Cache(1, H, 64, M, 64, Bq, "f32")
+    out = cache.new_output()
+    for t in range(4):                                  # the frame that overflows the budget is all infinite, and is evicted
+        q, k, v = (torch.randn(1, M, H, 64, generator=gen) for _ in range(3))
+        r = torch.ones(1, M, 64)
+        if t == 3:
+            k[:] = float("inf"); v[:] = float("nan"); r[:] = 0.01
+        cache.step(q.cuda(), k.cuda(), v.cuda(), r.cuda(), None, out)
+    e = cache.export(0)
+    keep = np.isfinite(e["k"]).all(axis=(1, 2))
+    cache.import_(0, 4, e["ids"][keep], e["k"][keep], e["v"][keep], e["ss"][keep], e["flags"][keep])
+    q, k, v = (torch.randn(1, 1, H, 64, generator=gen).repeat(1, M, 1, 1) for _ in range(3))
+    cache.step(q.cuda(), k.cuda(), v.cuda(), torch.ones(1, M, 64).cuda(), None, out)
+    assert torch.isfinite(out).all()
+    cache.close()
