@@ -243,7 +243,9 @@ int ovggt_cache_status(ovggt_cache* c, int layer, int32_t* status, void* hip_str
  * buffers in slot order: ids uint32[n], k and v [n, N_h, d] in the handle's
  * dtype, ss float[n], flags uint8[n].  Any output pointer may be NULL.  Serves
  * tests and checkpointing.  For bf16 handles K and V come back as bf16(half(x)):
- * equal to the appended value whenever that is a normal half number. */
+ * equal to the appended value whenever that is a normal half number; they are converted on the
+ * device, with the handle's workspace as the staging area (here and in ovggt_cache_import), so an
+ * attention call on the handle must be ordered before or after, like any two calls on one handle. */
 int ovggt_cache_export(ovggt_cache* c, int layer, uint32_t* ids, void* k, void* v, float* ss,
                        uint8_t* flags, void* hip_stream);
 

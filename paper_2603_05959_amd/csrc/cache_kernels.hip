@@ -210,6 +210,56 @@ hipError_t launch_set_protect(const Geom& g, char* meta, int layer0, int nl, int
   return hipGetLastError();
 }
 
+// --------------------------------------------------------------------------
+// Checkpoints of bf16 handles.  The host's layout is token-major bf16 [n][H][d], the cache is
+// head-major half; conversion and transposition run here, through a staging area in device memory,
+// so that K and V cross the bus in whole buffers.  One thread per 16-byte piece, consecutive in the
+// staging area (128-byte runs in the cache); a pure copy, bound by HBM and dwarfed by the bus.
+// 4096 tokens of 16 heads, out and in again and one frame on top: 131.6 ms with both done on the
+// host, 1.84 ms like this, of which 1.64 ms are four copies of 8.4 MB from and to pageable memory.
+__device__ inline uint32_t half_to_bf16_bits(uint32_t h) {
+  if ((h & 0x7FFFu) > 0x7C00u) return 0x7FC0u | (h & 0x8000u);         // NaN stays NaN
+  uint32_t u = __float_as_uint(__half2float(__ushort_as_half((unsigned short)h)));
+  u += 0x7FFFu + ((u >> 16) & 1u);                                     // round to nearest even
+  return u >> 16;
+}
+__device__ inline uint32_t bf16_to_half_bits(uint32_t b) {
+  const float f = __uint_as_float(b << 16);
+  if (f != f) return 0x7E00u;
+  return __half_as_ushort(__float2half_rn(fminf(fmaxf(f, -65504.f), 65504.f)));
+}
+
+// Slots [slot0, slot0 + rows) of one layer; stage: K rows, then V rows.
+template <bool TO_STAGE>
+__global__ void __launch_bounds__(256)
+checkpoint_kernel(Geom g, char* kv, int layer, int slot0, int rows, char* stage) {
+  const size_t total = (size_t)rows * g.H * 8;
+  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= total) return;
+  const int piece = (int)(i & 7);
+  const size_t rh = i >> 3;
+  const size_t row = rh / g.H;
+  const int h = (int)(rh - row * g.H);
+  char* cache = (blockIdx.y ? layer_v(kv, g, layer) : layer_k(kv, g, layer)) + ((size_t)h * g.cap + slot0 + row) * 128 + piece * 16;
+  char* host = stage + (blockIdx.y ? total * 16 : 0) + i * 16;
+  const uint4 w = *(const uint4*)(TO_STAGE ? cache : host);
+  uint32_t x[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const uint32_t lo = x[j] & 0xFFFFu, hi = x[j] >> 16;
+    x[j] = TO_STAGE ? half_to_bf16_bits(lo) | half_to_bf16_bits(hi) << 16 : bf16_to_half_bits(lo) | bf16_to_half_bits(hi) << 16;
+  }
+  *(uint4*)(TO_STAGE ? host : cache) = uint4{x[0], x[1], x[2], x[3]};
+}
+
+hipError_t launch_checkpoint(const Geom& g, char* kv, int layer, int slot0, int rows, char* stage, bool to_stage, hipStream_t s) {
+  const size_t total = (size_t)rows * g.H * 8;
+  dim3 grid((unsigned)((total + 255) / 256), 2);
+  if (to_stage) hipLaunchKernelGGL(checkpoint_kernel<true>, grid, dim3(256), 0, s, g, kv, layer, slot0, rows, stage);
+  else hipLaunchKernelGGL(checkpoint_kernel<false>, grid, dim3(256), 0, s, g, kv, layer, slot0, rows, stage);
+  return hipGetLastError();
+}
+
 hipError_t launch_compact(const Geom& g, char* kv, char* meta, int layer0, int nl, hipStream_t s) {
   dim3 grid((unsigned)g.M, (unsigned)nl);      // at most M entries move per frame
   hipLaunchKernelGGL(compact_kernel, grid, dim3(256), 0, s, g, kv, meta, layer0);

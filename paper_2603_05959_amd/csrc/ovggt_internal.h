@@ -147,6 +147,10 @@ hipError_t launch_centroid_protect(const Geom& g, char* kv, char* meta, int laye
 hipError_t launch_set_protect(const Geom& g, char* meta, int layer0, int nl, int n, uint32_t gid_lo,
                               const uint8_t* mask, int on, hipStream_t s);
 
+// Checkpoints of bf16 handles: rows [slot0, slot0 + rows) of a layer's K and V between the cache and a staging
+// area laid out as the host sees them (bf16 [rows][H][d], K then V; 2 * rows * H * 128 bytes).
+hipError_t launch_checkpoint(const Geom& g, char* kv, int layer, int slot0, int rows, char* stage, bool to_stage, hipStream_t s);
+
 // Apply the move list to K, V and the per-slot metadata.
 hipError_t launch_compact(const Geom& g, char* kv, char* meta, int layer0, int nl, hipStream_t s);
 
