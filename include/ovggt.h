@@ -134,7 +134,8 @@ int ovggt_cache_init(ovggt_cache** out, const ovggt_config* cfg,
  * fp32 (f32 MFMA, fp32 softmax).  Accuracy of bf16 runs: the rounded query makes a logit of magnitude x
  * (after the scale, in units of ln 2) uncertain by about x * 2^-12, so the
  * output error relative to the output's RMS is a few 1e-3 for logits of unit
- * spread and approaches 2e-2 when their spread reaches 16.  Range of bf16 runs: K
+ * spread and approaches 2e-2 when their spread reaches 16 (launches too small for that kernel
+ * take one that does not round the scaled query).  Range of bf16 runs: K
  * and V elements beyond +-65504 saturate when cached (OVGGT_STATUS_VRANGE); a query
  * element whose product with scale*log2(e) lies beyond +-65504 is clamped to that
  * bound without a status bit (a finite result instead of NaN; such logits are far

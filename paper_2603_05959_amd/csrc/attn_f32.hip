@@ -17,55 +17,39 @@
 // wait for is K and V out of L2 (11 TB/s: a 16-query block re-reads both).  Blocks of
 // 32 queries halve that traffic but fill the chip worse (528 instead of 1056 blocks
 // for 256 CUs) and took 10 to 20 % longer over every size from 17 to 1041 queries.
-#include "ovggt_internal.h"
+#include "attn_parts.h"
 
 namespace ovggt {
 
-typedef __attribute__((ext_vector_type(4))) float f32x4;
-
 constexpr float kF32Lag = 8.0f;         // the softmax reference may lag the running maximum by 2^8
-constexpr int kF32Rows = 16;            // queries of a workgroup
-constexpr int kF32Waves = 8;
-constexpr int kF32Threads = 64 * kF32Waves;
-constexpr int kF32Pitch = 68;           // floats per row of the merge area (64 + 4: rows start on different banks)
-constexpr int kF32RecFloats = kF32Rows * 64 + 2 * kF32Rows;      // one part's O rows, then references and weight sums
-constexpr int kF32MaxSplits = 16;
+constexpr int kF32Rows = kPartRows;     // queries of a workgroup
 constexpr int kF32MaxRecs = 4096;       // parts of a split launch (17 MB of workspace at most)
 
-// Workspace of an fp32 handle: an arrival counter per query block, then one record per part.
-static size_t f32_counter_bytes() { return (size_t)kF32MaxRecs / 2 * sizeof(uint32_t); }
+// Workspace of an fp32 handle: one record per part.
 size_t attn_f32_ws_bytes(int layer_heads, int tokens_per_frame) {
   const long blocks = (long)((tokens_per_frame + kF32Rows - 1) / kF32Rows) * layer_heads;
-  const long recs = blocks * kF32MaxSplits < kF32MaxRecs ? blocks * kF32MaxSplits : kF32MaxRecs;
-  return f32_counter_bytes() + (size_t)recs * kF32RecFloats * sizeof(float);
+  const long recs = blocks * kMaxSplits < kF32MaxRecs ? blocks * kMaxSplits : kF32MaxRecs;
+  return (size_t)recs * part_rec_floats(1) * sizeof(float);
 }
 
 struct AttnF32Params {
   const char* kv;
+  char* meta;
   const float* q;
   float* out;
-  uint32_t* arrive;           // one counter per query block, zero between launches
   float* recs;
   int layer0, n_total, QB, n_work, splits;
   float c;                    // softmax scale * log2(e)
 };
 
-__device__ inline void store_through(float* p, const f32x4& v) {
-  const float2 a = {v[0], v[1]}, b = {v[2], v[3]};
-  __hip_atomic_store((unsigned long long*)p, __builtin_bit_cast(unsigned long long, a), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  __hip_atomic_store((unsigned long long*)p + 1, __builtin_bit_cast(unsigned long long, b), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
 // A workgroup takes 16 queries of one head over one of `splits` equal ranges of
 // the slots; its waves share the 16-slot tiles of the range (wave w: every 8th
 // from the w-th) and merge through LDS.  With more than one range, the parts go
 // to memory and the workgroup that arrives last for a query block merges them.
-__global__ void __launch_bounds__(kF32Threads)
+__global__ void __launch_bounds__(kPartThreads)
 attn_f32_kernel(Geom g, AttnF32Params p) {
-  constexpr int W = kF32Waves;
-  __shared__ float mO[W][kF32Rows][kF32Pitch];
-  __shared__ float mM[W][kF32Rows], mL[W][kF32Rows];
-  __shared__ uint32_t is_last;
+  constexpr int W = kPartWaves;
+  __shared__ MergeArea<1> area;
   // Consecutive workgroups of an XCD walk the query blocks of one range of one head, whose K and V
   // rows then come from that XCD's L2.
   const int idx = (int)(blockIdx.x & 7) * (int)(gridDim.x >> 3) + (int)(blockIdx.x >> 3);
@@ -89,10 +73,10 @@ attn_f32_kernel(Geom g, AttnF32Params p) {
   const int t0 = (int)((long)nt * sp / p.splits), t1 = (int)((long)nt * (sp + 1) / p.splits);
   const bool ragged = (n_total & 15) != 0;
   const float c = p.c;
-  f32x4 kf[4], vf[4], O[4];
-  float m = -3.402823466e38f, l = 0.f;
+  f32x4 kf[4], vf[4], O[1][4];
+  float m[1] = {-3.402823466e38f}, l[1] = {0.f};
 #pragma unroll
-  for (int d = 0; d < 4; ++d) O[d] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int d = 0; d < 4; ++d) O[0][d] = f32x4{0.f, 0.f, 0.f, 0.f};
   // rows at or beyond n_total are never read (they may hold anything): the last resident row stands in
   auto load_k = [&](int t) {
     const float* kp = kbase + (size_t)min(t * 16 + l16, n_total - 1) * 64 + 4 * gl;
@@ -131,101 +115,33 @@ attn_f32_kernel(Geom g, AttnF32Params p) {
     // The reference m follows the maximum only when it is passed by 2^8 (weights are fp32: no
     // accuracy is lost), so most tiles rescale nothing and look at no other lane.
     const float mx = fmaxf(fmaxf(S[0], S[1]), fmaxf(S[2], S[3])) * c;
-    if (__builtin_amdgcn_ballot_w64(mx > m + kF32Lag) != 0ull) {
+    if (__builtin_amdgcn_ballot_w64(mx > m[0] + kF32Lag) != 0ull) {
       float x = fmaxf(mx, __shfl_xor(mx, 16, 64));
       x = fmaxf(x, __shfl_xor(x, 32, 64));
-      const float mn = fmaxf(m, x), a = __builtin_amdgcn_exp2f(m - mn);
-      m = mn;
-      l *= a;
+      const float mn = fmaxf(m[0], x), a = __builtin_amdgcn_exp2f(m[0] - mn);
+      m[0] = mn;
+      l[0] *= a;
 #pragma unroll
-      for (int d = 0; d < 4; ++d) O[d] *= a;
+      for (int d = 0; d < 4; ++d) O[0][d] *= a;
     }
 #pragma unroll
-    for (int i = 0; i < 4; ++i) S[i] = __builtin_amdgcn_exp2f(fmaf(S[i], c, -m));
-    l += (S[0] + S[1]) + (S[2] + S[3]);
+    for (int i = 0; i < 4; ++i) S[i] = __builtin_amdgcn_exp2f(fmaf(S[i], c, -m[0]));
+    l[0] += (S[0] + S[1]) + (S[2] + S[3]);
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
-      for (int d = 0; d < 4; ++d) O[d] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[i][d], S[i], O[d], 0, 0, 0);
+      for (int d = 0; d < 4; ++d) O[0][d] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[i][d], S[i], O[0][d], 0, 0, 0);
     load_v(tn);
   }
 
-  // ---- merge of the waves: the common reference first, then the rescaled parts
-  l += __shfl_xor(l, 16, 64);
-  l += __shfl_xor(l, 32, 64);
-  if (gl == 0) { mM[wave][l16] = m; mL[wave][l16] = l; }
-  __syncthreads();
-  {
-    float mt = mM[0][l16];
-#pragma unroll
-    for (int w = 1; w < W; ++w) mt = fmaxf(mt, mM[w][l16]);
-    const float a = __builtin_amdgcn_exp2f(m - mt);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const f32x4 o = {O[0][i] * a, O[1][i] * a, O[2][i] * a, O[3][i] * a};
-      *(f32x4*)&mO[wave][l16][16 * gl + 4 * i] = o;
-    }
-  }
-  __syncthreads();
-  const int row = (int)threadIdx.x >> 4, piece = (int)threadIdx.x & 15;      // the first four waves: 16 rows of 16 pieces
-  f32x4 o = {0.f, 0.f, 0.f, 0.f};
-  float ls = 0.f, mt = 0.f;
-  if (row < kF32Rows) {
-    mt = mM[0][row];
-#pragma unroll
-    for (int w = 1; w < W; ++w) mt = fmaxf(mt, mM[w][row]);
-#pragma unroll
-    for (int w = 0; w < W; ++w) {
-      ls += mL[w][row] * __builtin_amdgcn_exp2f(mM[w][row] - mt);
-      o += *(const f32x4*)&mO[w][row][4 * piece];
-    }
-  }
-  if (p.splits > 1) {
-    // Parts are written through to device-coherent memory, so a wave waits for its own stores only;
-    // the counter is a relaxed device-scope atomic and the last arrival invalidates its caches.
-    const size_t first = ((size_t)lh * p.splits) * p.QB + qb;        // record of range 0; the ranges are QB apart
-    if (row < kF32Rows) {
-      float* rec = p.recs + (first + (size_t)sp * p.QB) * kF32RecFloats;
-      store_through(rec + row * 64 + 4 * piece, o);
-      if (piece == 0) {
-        __hip_atomic_store(rec + kF32Rows * 64 + row, mt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(rec + kF32Rows * 65 + row, ls, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      }
-    }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      uint32_t* cnt = p.arrive + (size_t)lh * p.QB + qb;
-      const bool last = __hip_atomic_fetch_add(cnt, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)p.splits - 1u;
-      if (last) {
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-        __hip_atomic_store(cnt, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      }
-      is_last = last ? 1u : 0u;
-    }
-    __syncthreads();
-    if (!is_last || row >= kF32Rows) return;
-    float pm[kF32MaxSplits];
-    mt = -INFINITY;
-#pragma unroll
-    for (int s = 0; s < kF32MaxSplits; ++s) {          // ranges beyond the last repeat it, with no weight
-      pm[s] = p.recs[(first + (size_t)min(s, p.splits - 1) * p.QB) * kF32RecFloats + kF32Rows * 64 + row];
-      mt = fmaxf(mt, pm[s]);
-    }
-    o = f32x4{0.f, 0.f, 0.f, 0.f};
-    ls = 0.f;
-#pragma unroll 4
-    for (int s = 0; s < p.splits; ++s) {
-      const float* rec = p.recs + (first + (size_t)s * p.QB) * kF32RecFloats;
-      const float a = __builtin_amdgcn_exp2f(rec[kF32Rows * 64 + row] - mt);
-      ls += rec[kF32Rows * 65 + row] * a;
-      o += *(const f32x4*)(rec + row * 64 + 4 * piece) * a;
-    }
-  }
-  if (row < kF32Rows && q0 + row < g.M) {
-    const f32x4 r = {o[0] / ls, o[1] / ls, o[2] / ls, o[3] / ls};
-    *(f32x4*)(p.out + (((size_t)li * g.M + q0 + row) * g.H + h) * 64 + 4 * piece) = r;
-  }
+  l[0] += __shfl_xor(l[0], 16, 64);
+  l[0] += __shfl_xor(l[0], 32, 64);
+  uint32_t* arrive = (uint32_t*)(layer_meta(p.meta, g, p.layer0 + li) + g.off_arrive) + (size_t)h * p.QB + qb;
+  const size_t first = (size_t)lh * p.splits * p.QB + qb;              // record of range 0; the ranges are QB apart
+  merge_and_write(area, O, m, l, sp, p.splits, arrive, p.recs + first * part_rec_floats(1), (size_t)p.QB * part_rec_floats(1),
+                     [&](int row, int piece, const f32x4& r) {
+                       if (q0 + row < g.M) *(f32x4*)(p.out + (((size_t)li * g.M + q0 + row) * g.H + h) * 64 + 4 * piece) = r;
+                     });
 }
 
 // Ranges per query block.  Fewer blocks than CUs: one range more for every CU that would idle, as long
@@ -239,8 +155,8 @@ static int f32_splits(long blocks, int n_tiles, long max_recs) {
   if (blocks < kCus) {
     s = kCus / blocks;
     if (s > n_tiles / 16) s = n_tiles / 16;
-    if (s > kF32MaxSplits) s = kF32MaxSplits;
-  } else if (blocks <= kF32MaxRecs / 2) {
+    if (s > kMaxSplits) s = kMaxSplits;
+  } else if (blocks <= kMaxArrive) {
     float best = 0.f;
     for (long k = 1; k <= 4 && n_tiles / k >= 64; ++k) {
       const long rounds = (blocks * k + kCus - 1) / kCus;
@@ -252,22 +168,21 @@ static int f32_splits(long blocks, int n_tiles, long max_recs) {
   return s < 1 ? 1 : (int)s;
 }
 
-hipError_t launch_attn_f32(const Geom& g, char* kv, int layer0, int nl, const void* q, void* out,
+hipError_t launch_attn_f32(const Geom& g, char* kv, char* meta, int layer0, int nl, const void* q, void* out,
                            int n_total, float scale, char* ws, size_t ws_bytes, hipStream_t s) {
   AttnF32Params p;
-  p.kv = kv; p.q = (const float*)q; p.out = (float*)out;
-  p.arrive = (uint32_t*)ws;
-  p.recs = (float*)(ws + f32_counter_bytes());
+  p.kv = kv; p.meta = meta; p.q = (const float*)q; p.out = (float*)out;
+  p.recs = (float*)ws;
   p.layer0 = layer0; p.n_total = n_total;
   p.QB = (g.M + kF32Rows - 1) / kF32Rows;
   p.c = scale * 1.4426950408889634f;
   const long blocks = (long)p.QB * g.H * nl;
-  const long max_recs = ws_bytes > f32_counter_bytes() ? (long)((ws_bytes - f32_counter_bytes()) / (kF32RecFloats * sizeof(float))) : 0;
+  const long max_recs = (long)(ws_bytes / (part_rec_floats(1) * sizeof(float)));
   p.splits = f32_splits(blocks, (n_total + 15) / 16, max_recs);
   const long work = blocks * p.splits;
   if (work > 0x7FFFFFF0L) return hipErrorInvalidValue;
   p.n_work = (int)work;
-  hipLaunchKernelGGL(attn_f32_kernel, dim3((unsigned)((work + 7) / 8 * 8)), dim3(kF32Threads), 0, s, g, p);
+  hipLaunchKernelGGL(attn_f32_kernel, dim3((unsigned)((work + 7) / 8 * 8)), dim3(kPartThreads), 0, s, g, p);
   return hipGetLastError();
 }
 

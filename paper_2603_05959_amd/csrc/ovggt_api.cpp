@@ -87,6 +87,7 @@ void make_geom(const ovggt_config& c, Geom* g) {
   g->off_dpart = off; off += c.score_mode == 1 ? up256((size_t)8 * kDivWavesPerWg * diversity_grid_x(g->cap, 1)) : 0;
   g->off_mvmap = off; off += up256((size_t)4 * g->M);
   g->off_hist = off;  off += up256((size_t)4 * kSelHistBins);
+  g->off_arrive = off; off += up256((size_t)4 * std::min<int64_t>(kMaxArrive, (int64_t)g->H * ((g->M + 15) / 16)));
   g->hybrid = c.score_mode == 1 ? 1 : 0;
   g->meta_layer_bytes = off;
 }
@@ -277,15 +278,22 @@ static int global_attn_impl(ovggt_cache* c, int layer, const void* q, const void
         for (hipEvent_t x : ev)
           if (x) c->prof_free.push_back(x);
     }
-    e = launch_attn_bf16(g, c->kv, l0, nl, q, out, n + g.M, c->scale, ws, ws_bytes, c->n_wgs,
-                         c->cfg.out_dtype == OVGGT_F32, s, have ? ev : nullptr);
+    if (attn_few_better(g, nl, n + g.M)) {                        // one kernel, merges included
+      e = have ? hipEventRecord(ev[0], s) : hipSuccess;
+      if (e == hipSuccess)
+        e = launch_attn_few(g, c->kv, c->meta, l0, nl, q, out, n + g.M, c->scale, ws, ws_bytes, c->cfg.out_dtype == OVGGT_F32, s);
+      for (int i = 1; i < 3 && have && e == hipSuccess; ++i) e = hipEventRecord(ev[i], s);
+    } else {
+      e = launch_attn_bf16(g, c->kv, l0, nl, q, out, n + g.M, c->scale, ws, ws_bytes, c->n_wgs,
+                           c->cfg.out_dtype == OVGGT_F32, s, have ? ev : nullptr);
+    }
     if (have) {
       c->prof_pending[OVGGT_PROF_ATTN].push_back({ev[0], ev[1]});
       c->prof_pending[OVGGT_PROF_COMBINE].push_back({ev[1], ev[2]});   // shares ev[1] as its start
     }
   } else {
     ProfScope ps(c, OVGGT_PROF_ATTN, s, prof_attn);
-    e = launch_attn_f32(g, c->kv, l0, nl, q, out, n + g.M, c->scale, ws, ws_bytes, s);
+    e = launch_attn_f32(g, c->kv, c->meta, l0, nl, q, out, n + g.M, c->scale, ws, ws_bytes, s);
   }
   if (e != hipSuccess) return OVGGT_ERR_HIP;
   for (int l = l0; l < l0 + nl; ++l) { c->n[l] = n + g.M; c->phase[l] = 1; }

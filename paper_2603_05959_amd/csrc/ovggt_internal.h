@@ -49,9 +49,13 @@ struct Geom {
   size_t off_mvmap;        // per slot B + j (j < M): the slot below B it moves to under the last selection, or kNoMove
   size_t off_hist;         // kSelHistBins counters: the selection's first-level histogram of the cached entries' score
                            // words, filled by all workgroups of a launch and zeroed again by the one that selects
+  size_t off_arrive;       // up to kMaxArrive counters of finished parts, one per (head, block of queries) whose slots several
+                           // workgroups share (attn_parts.h): zero between launches, so not in the workspace, whose contents
+                           // no launch may count on
 };
 
 constexpr int kSelHistBins = 2048;  // the 11 bits below the sign of a score word
+constexpr int kMaxArrive = 2048;    // query blocks of a launch whose slots may be split
 constexpr uint32_t kNoMove = 0xFFFFFFFFu;
 
 __host__ __device__ inline char* layer_k(char* kv, const Geom& g, int layer) {
@@ -77,9 +81,13 @@ hipError_t launch_append(const Geom& g, char* kv, char* meta, int layer0, int nl
                          const void* k_new, const void* v_new, int n, bool apply_moves, hipStream_t s);
 
 // Attention of M queries over n_total resident slots.
-hipError_t launch_attn_f32(const Geom& g, char* kv, int layer0, int nl, const void* q, void* out,
+hipError_t launch_attn_f32(const Geom& g, char* kv, char* meta, int layer0, int nl, const void* q, void* out,
                            int n_total, float scale, char* ws, size_t ws_bytes, hipStream_t s);
 size_t attn_f32_ws_bytes(int layer_heads, int tokens_per_frame);
+// The same over the half-precision cache of bf16 handles, for launches that attn_few_better names.
+hipError_t launch_attn_few(const Geom& g, char* kv, char* meta, int layer0, int nl, const void* q, void* out,
+                           int n_total, float scale, char* ws, size_t ws_bytes, bool out_f32, hipStream_t s);
+bool attn_few_better(const Geom& g, int nl, int n_total);
 // `ev` (optional, 3 events) are recorded before the main kernel, between it and
 // the combine kernel, and after the combine kernel.
 hipError_t launch_attn_bf16(const Geom& g, char* kv, int layer0, int nl, const void* q, void* out,

@@ -1,0 +1,71 @@
+"""Small launches of bf16 handles against fp64 softmax over the same rows, at the edges of the kernel they
+take: 16 queries to a group, one, two or four groups to a workgroup, 32 slots to a tile, eight waves and up
+to 16 slot ranges; and sizes on both sides of the line to the kernel for large ones."""
+import numpy as np
+import pytest
+
+from paper_2603_05959_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("M,n_old,H,layers,out", [
+    (1, 1, 1, 1, "f32"), (1, 30, 3, 1, "bf16"), (1, 31, 1, 2, "f32"), (1, 32, 1, 1, "f32"),   # one tile, ragged and full; two
+    (15, 241, 2, 1, "f32"), (16, 240, 2, 1, "bf16"), (17, 240, 2, 2, "f32"),   # eight tiles: one a wave; one query of the next block
+    (1, 4095, 1, 1, "f32"), (5, 4200, 3, 1, "bf16"),                # the most ranges; ranges of unequal length
+    (33, 16000, 16, 1, "f32"), (64, 8000, 16, 1, "bf16"),           # two groups, the last one of padding; two full ones
+    (128, 16384, 16, 1, "f32"), (97, 4096, 16, 12, "bf16"),         # four groups, split and not
+    (1041, 4096, 1, 1, "f32"), (513, 2048, 4, 1, "f32"),            # many blocks of few heads
+    (700, 4096, 16, 1, "f32"), (400, 4096, 16, 1, "f32"),           # the large kernel, and near the line
+])
+def test_matches_fp64_softmax(M, n_old, H, layers, out):
+    import torch
+    gen = torch.Generator().manual_seed(M * 1000 + n_old)
+    cache = B.Cache(layers, H, 64, M, 64, max(n_old, M), "bf16", out_dtype=out)
+    rnd = lambda *s: torch.randn(s, generator=gen, dtype=torch.float32).bfloat16()
+    old = [(rnd(n_old, H, 64), rnd(n_old, H, 64)) for _ in range(layers)]
+    for l, (k, v) in enumerate(old):
+        cache.import_(l, 3 + n_old // M, np.arange(n_old, dtype=np.uint32), k.view(torch.int16).numpy().view(np.uint16),
+                      v.view(torch.int16).numpy().view(np.uint16), np.ones(n_old, np.float32), np.zeros(n_old, np.uint8))
+    o = cache.new_output()
+    for rep in range(2):                                # the arrival counters are back at zero for the second frame
+        q, k, v = (rnd(layers, M, H, 64) for _ in range(3))
+        q[:, 0] *= 6.0                                  # one dominant key, and a reference that is passed by far
+        cache.step(q.cuda(), k.cuda(), v.cuda(), torch.ones(layers, M, 64, device="cuda").bfloat16(), None, o)
+        got = o.double()
+        for l in sorted({0, layers - 1}):
+            # the cache holds half(bf16): exact for all but values below 2^-14
+            kk, vv = (torch.cat([a, b]).half().double().cuda() for a, b in ((old[l][0], k[l]), (old[l][1], v[l])))
+            for h in sorted({0, H // 2, H - 1}):
+                p = torch.softmax(torch.mm(q[l, :, h].double().cuda(), kk[:, h].t().contiguous()) / 8.0, dim=-1)
+                ref = torch.mm(p, vv[:, h])
+                err = ((got[l, :, h] - ref).norm() / ref.norm()).item()
+                # weights rounded to 11 bits (relative errors of 2^-11 / sqrt(3) at most in the mean, as random signs add up);
+                # the kernel for large launches rounds the scaled queries to 11 bits too; a bf16 output has 8 bits
+                assert err < 2.0 ** -11 + (2.0 ** -11 if M in (400, 700) else 0.0) + (2.0 ** -9 if out == "bf16" else 0.0), (rep, l, h, err)
+        e = [cache.export(l) for l in range(layers)]
+        old = [tuple(torch.from_numpy(x[n]).bfloat16() for n in "kv") for x in e]
+    cache.close()
+
+
+def test_rows_behind_the_last_slot_carry_no_weight():
+    """Evicted entries stay in memory behind the resident ones, NaN among them."""
+    import torch
+    M, H, Bq = 5, 2, 19
+    gen = torch.Generator().manual_seed(2)
+    cache = B.Cache(1, H, 64, M, 64, Bq, "bf16")
+    o = cache.new_output()
+    for t in range(4):                                  # the frame that overflows the budget is all NaN, and is evicted
+        q, k, v = (torch.randn(1, M, H, 64, generator=gen) for _ in range(3))
+        r = torch.ones(1, M, 64)
+        if t == 3:
+            k[:] = float("nan"); v[:] = float("nan"); r[:] = 0.01
+        cache.step(*(x.bfloat16().cuda() for x in (q, k, v, r)), None, o)
+    e = cache.export(0)
+    keep = np.isfinite(e["k"]).all(axis=(1, 2))
+    bits = [torch.from_numpy(e[n][keep]).bfloat16().view(torch.int16).numpy().view(np.uint16) for n in "kv"]
+    cache.import_(0, 4, e["ids"][keep], *bits, e["ss"][keep], e["flags"][keep])
+    q, k, v = (torch.randn(1, 1, H, 64, generator=gen).repeat(1, M, 1, 1).bfloat16().cuda() for _ in range(3))
+    cache.step(q, k, v, torch.ones(1, M, 64).bfloat16().cuda(), None, o)
+    assert torch.isfinite(o).all()
+    cache.close()
