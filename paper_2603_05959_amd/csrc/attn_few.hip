@@ -2,7 +2,7 @@
 // tokens per frame (the camera head's one), few heads, short caches.  Those items are mostly padding or hold a
 // tile or two here, and what counts is how fast K and V arrive, how many parts are merged and how many launches
 // it takes: one, merges included.  Latency bounds it at the small end (one query of 16 heads over 189 slots: 5.8 us
-// of a step's 21), the rate of K and V out of L2 and the vector work per score at the large one (256 queries of 192
+// of a step's 19), the rate of K and V out of L2 and the vector work per score at the large one (256 queries of 192
 // heads over 16640 slots: 330 us, 630 TFLOP/s).
 //
 // A workgroup takes G groups of 16 queries of one head over one of `splits` ranges of the slots, on
