@@ -307,9 +307,20 @@ int ovggt_dap_step(ovggt_dap* d, int64_t t, double rho, const float* conf, int64
 int ovggt_dap_active(const ovggt_dap* d, int64_t* frames, int32_t cap, int32_t* n);
 int ovggt_dap_destroy(ovggt_dap* d);
 
-/* Host-only: how the bf16 attention launch of `layers_in_launch` layers (1 or cfg->n_layers) over
- * n_total resident slots would be divided among n_wgs workgroups (the library uses one per compute
- * unit).  Walks the plan as the kernel does and checks that every (head, query block, key tile) is
+/* Host-only: which attention kernel a launch of `layers_in_launch` layers (1 or cfg->n_layers) over
+ * n_total resident slots takes on a device of n_wgs compute units, and how it is cut.  out[0] = the
+ * kernel: work items of 128 queries and a merge pass (OVGGT_ATTN_ITEMS, see ovggt_attn_plan_stats),
+ * the one for small launches (OVGGT_ATTN_FEW) or the fp32 one; out[1] = queries of a workgroup at a
+ * time; out[2] = ranges that the slots are cut into, a workgroup for each (0 for OVGGT_ATTN_ITEMS);
+ * out[3] = workgroups.  OVGGT_OK, ERR_ARG (bad config or sizes), ERR_STATE (more workgroups than a
+ * launch may have). */
+enum { OVGGT_ATTN_ITEMS = 0, OVGGT_ATTN_FEW = 1, OVGGT_ATTN_F32 = 2 };
+int ovggt_attn_route(const ovggt_config* cfg, int32_t layers_in_launch, int32_t n_total, int32_t n_wgs, int32_t* out);
+
+/* Host-only: how a bf16 attention launch of `layers_in_launch` layers (1 or cfg->n_layers) over
+ * n_total resident slots that takes the kernel of 128-query items (OVGGT_ATTN_ITEMS above; the plan
+ * exists for every size, whether or not it is the one launched) is divided among n_wgs workgroups
+ * (the library uses one per compute unit).  Walks the plan as the kernel does and checks that every (head, query block, key tile) is
  * covered exactly once and that no workgroup needs more partial records than it owns.
  * out[0..7] = workgroups, rounds per workgroup, tile segments, 1 if chunks are cost-balanced, most
  * pieces given to one workgroup, fewest and most tiles given to one workgroup, work items in which

@@ -26,8 +26,9 @@ EXPORTS = (
     "ovggt_profile_enable", "ovggt_profile_read", "ovggt_profile_overhead", "ovggt_strerror",
     "ovggt_cache_set_protect", "ovggt_dap_create", "ovggt_dap_step", "ovggt_dap_active", "ovggt_dap_destroy",
     "ovggt_attn_plan_stats", "ovggt_cache_flush", "ovggt_cache_advance",
-    "ovggt_global_attn_static_ws",
+    "ovggt_global_attn_static_ws", "ovggt_attn_route",
 )
+ATTN_KERNELS = ("items", "few", "f32")                # ovggt_attn_route's out[0]
 PROF_CLASSES = ("append", "attn", "combine", "score_select", "compact")
 
 
@@ -85,6 +86,7 @@ def lib() -> C.CDLL:
     L.ovggt_dap_active.argtypes = [vp, C.POINTER(i64), i32, C.POINTER(i32)]
     L.ovggt_dap_destroy.argtypes = [vp]
     L.ovggt_attn_plan_stats.argtypes = [cfgp, i32, i32, i32, C.POINTER(i32), C.POINTER(C.c_float)]
+    L.ovggt_attn_route.argtypes = [cfgp, i32, i32, i32, C.POINTER(i32)]
     L.ovggt_strerror.argtypes = [C.c_int]
     L.ovggt_strerror.restype = C.c_char_p
     for name in EXPORTS:
@@ -247,6 +249,12 @@ def ovggt_attn_plan_stats(cfg: ovggt_config, layers_in_launch: int, n_total: int
     d = dict(zip(keys, list(out)))
     d["cost_max"], d["cost_mean"] = cost[0], cost[1]
     return d
+
+
+def ovggt_attn_route(cfg: ovggt_config, layers_in_launch: int, n_total: int, n_wgs: int = 256) -> dict:
+    out = (C.c_int32 * 4)()
+    _check(lib().ovggt_attn_route(C.byref(cfg), layers_in_launch, n_total, n_wgs, out), "ovggt_attn_route")
+    return {"kernel": ATTN_KERNELS[out[0]], "rows": out[1], "ranges": out[2], "workgroups": out[3]}
 
 
 def ovggt_profile_enable(h, level: int, every: int = 1) -> None:

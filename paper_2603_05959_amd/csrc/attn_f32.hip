@@ -149,18 +149,17 @@ attn_f32_kernel(Geom g, AttnF32Params p) {
 // with 1 range, 33 with 4, 29 with 16; 700 queries of one head over 4796: 68 with 1, 36 with 4, 41 with 6;
 // 17 of 8 heads over 1017: 28 with 1, 24 with 4).  More blocks than CUs: ranges smooth the last,
 // partly filled round (1056 blocks = 4.1 a CU: 286 us with 1 range, 259 with 2, 250 with 3 and with 16).
-static int f32_splits(long blocks, int n_tiles, long max_recs) {
-  constexpr long kCus = 256;
+static int f32_splits(long blocks, int n_tiles, long max_recs, long cus) {
   long s = 1;
-  if (blocks < kCus) {
-    s = kCus / blocks;
+  if (blocks < cus) {
+    s = cus / blocks;
     if (s > n_tiles / 16) s = n_tiles / 16;
     if (s > kMaxSplits) s = kMaxSplits;
   } else if (blocks <= kMaxArrive) {
     float best = 0.f;
     for (long k = 1; k <= 4 && n_tiles / k >= 64; ++k) {
-      const long rounds = (blocks * k + kCus - 1) / kCus;
-      const float full = (float)(blocks * k) / (float)(rounds * kCus);
+      const long rounds = (blocks * k + cus - 1) / cus;
+      const float full = (float)(blocks * k) / (float)(rounds * cus);
       if (full > best + 0.02f) { best = full; s = k; }
     }
   }
@@ -168,21 +167,28 @@ static int f32_splits(long blocks, int n_tiles, long max_recs) {
   return s < 1 ? 1 : (int)s;
 }
 
+AttnSplit attn_f32_split(const Geom& g, int nl, int n_total, size_t ws_bytes, int n_wgs) {
+  AttnSplit sp;
+  sp.rows = kF32Rows;
+  const long blocks = (long)((g.M + kF32Rows - 1) / kF32Rows) * g.H * nl;
+  sp.ranges = f32_splits(blocks, (n_total + 15) / 16, (long)(ws_bytes / (part_rec_floats(1) * sizeof(float))), n_wgs);
+  sp.work = blocks * sp.ranges;
+  return sp;
+}
+
 hipError_t launch_attn_f32(const Geom& g, char* kv, char* meta, int layer0, int nl, const void* q, void* out,
-                           int n_total, float scale, char* ws, size_t ws_bytes, hipStream_t s) {
+                           int n_total, float scale, char* ws, size_t ws_bytes, int n_wgs, hipStream_t s) {
   AttnF32Params p;
+  const AttnSplit sp = attn_f32_split(g, nl, n_total, ws_bytes, n_wgs);
   p.kv = kv; p.meta = meta; p.q = (const float*)q; p.out = (float*)out;
   p.recs = (float*)ws;
   p.layer0 = layer0; p.n_total = n_total;
   p.QB = (g.M + kF32Rows - 1) / kF32Rows;
   p.c = scale * 1.4426950408889634f;
-  const long blocks = (long)p.QB * g.H * nl;
-  const long max_recs = (long)(ws_bytes / (part_rec_floats(1) * sizeof(float)));
-  p.splits = f32_splits(blocks, (n_total + 15) / 16, max_recs);
-  const long work = blocks * p.splits;
-  if (work > 0x7FFFFFF0L) return hipErrorInvalidValue;
-  p.n_work = (int)work;
-  hipLaunchKernelGGL(attn_f32_kernel, dim3((unsigned)((work + 7) / 8 * 8)), dim3(kPartThreads), 0, s, g, p);
+  p.splits = sp.ranges;
+  if (sp.work > 0x7FFFFFF0L) return hipErrorInvalidValue;
+  p.n_work = (int)sp.work;
+  hipLaunchKernelGGL(attn_f32_kernel, dim3((unsigned)((sp.work + 7) / 8 * 8)), dim3(kPartThreads), 0, s, g, p);
   return hipGetLastError();
 }
 

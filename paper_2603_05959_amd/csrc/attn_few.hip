@@ -189,32 +189,32 @@ attn_few_kernel(Geom g, AttnFewParams p) {
 // Ranges of the slots for each block of queries: one more for every CU that would idle, as long as a range keeps a
 // tile for each wave (ranges for two workgroups a CU: 24.7 -> 21.7 us at 1 query of 2 heads over 2049 slots, but
 // 37 -> 57 at 128 of 16 over 4224).
-static long few_splits(long blocks, int n_total) {
-  if (blocks >= kMaxAttnWgs) return 1;
+static long few_splits(long blocks, int n_total, int cus) {
+  if (blocks >= cus) return 1;
   const long most = ((n_total + 31) / 32 + kPartWaves - 1) / kPartWaves;
-  long s = kMaxAttnWgs / blocks;
+  long s = cus / blocks;
   if (s > most) s = most;
   return s > kMaxSplits ? kMaxSplits : s;
 }
 
 // What a launch with G groups of 16 queries a workgroup takes beside its fixed part, in us: what the larger
-// merge adds, then the rate at which all CUs take 16 queries past a slot (fit over 1 to 1041 queries, 600 to 65 K
+// merge adds, then the rate at which 256 CUs take 16 queries past a slot (fit over 1 to 1041 queries, 600 to 65 K
 // slots, 2 to 192 heads: 51 million such units take 1060 us with G = 1, 545 with 2 and 330 with 4), over the share of
 // the CUs that the last round of workgroups fills (520 queries of 16 heads over 2568 slots, 272 workgroups with
 // G = 2: 51.6 us, the time of 512).
-static float few_cost(int G, const Geom& g, int nl, int n_total) {
+static float few_cost(int G, const Geom& g, int nl, int n_total, int cus) {
   const long blocks = (long)((g.M + G * kPartRows - 1) / (G * kPartRows)) * g.H * nl;
   const float extra = G == 1 ? 0.f : G == 2 ? 2.f : 8.f, rate = G == 1 ? 20.8e-6f : G == 2 ? 11.5e-6f : 7.0e-6f;
-  const long wgs = blocks * few_splits(blocks, n_total), rounds = (wgs + kMaxAttnWgs - 1) / kMaxAttnWgs;
-  const float fill = (float)wgs / (float)(rounds * kMaxAttnWgs);
-  return extra + rate * (float)(blocks * G) * (float)n_total / fill;
+  const long wgs = blocks * few_splits(blocks, n_total, cus), rounds = (wgs + cus - 1) / cus;
+  const float fill = (float)wgs / (float)(rounds * cus);
+  return extra + rate * (256.f / (float)cus) * (float)(blocks * G) * (float)n_total / fill;
 }
 
 // More groups read K and V less often, fewer fill the chip with less work and merge sooner.
-static int few_groups(const Geom& g, int nl, int n_total) {
+static int few_groups(const Geom& g, int nl, int n_total, int cus) {
   int best = 1;
   for (int G = 2; G <= 4; G *= 2)
-    if (few_cost(G, g, nl, n_total) < few_cost(best, g, nl, n_total)) best = G;
+    if (few_cost(G, g, nl, n_total, cus) < few_cost(best, g, nl, n_total, cus)) best = G;
   return best;
 }
 
@@ -224,11 +224,11 @@ static int few_groups(const Geom& g, int nl, int n_total) {
 // The margin of a fifth keeps sizes where the two are level on the older path.  Step times there and here,
 // 16 heads: 1 query over 4097 slots 47.0 and 25.6 us, 64 over 16448 69 and 42, 128 over 4224 in 12 layers 196 and 85,
 // 256 over 16640 63 and 58 (stays), 700 over 4796 50 and 55; 1041 queries of 2 heads over 5137 61 and 38.
-bool attn_few_better(const Geom& g, int nl, int n_total) {
+bool attn_few_better(const Geom& g, int nl, int n_total, int n_wgs) {
   // a tile; the ends of a run, in tiles, alone and behind another round's; runs of a workgroup that takes cut items
   constexpr float kTileUs = 1.7f, kRunTiles = 7.f, kRoundTiles = 6.5f, kRuns = 1.25f;
   const long pairs = ((long)g.H * nl + 1) / 2, QB = (g.M + kQueryTile - 1) / kQueryTile, T = (n_total + kSlotTile - 1) / kSlotTile;
-  constexpr long wgs = kMaxAttnWgs, per_xcd = wgs / 8;
+  const long wgs = n_wgs, per_xcd = wgs / 8;
   float tiles, recs;      // of the busiest workgroup, run overhead included; of an item, where the merge pass has no table of them
   if (attn_whole_items(g.H * nl, (int)QB, (int)wgs)) {
     const long items = pairs / 8 * QB, left = items % per_xcd;
@@ -244,33 +244,40 @@ bool attn_few_better(const Geom& g, int nl, int n_total) {
     if (table) recs = 0.f;
   }
   const float there = kTileUs * tiles + 4.f + 0.6f * recs;
-  return 1.2f * few_cost(few_groups(g, nl, n_total), g, nl, n_total) < there;
+  return 1.2f * few_cost(few_groups(g, nl, n_total, n_wgs), g, nl, n_total, n_wgs) < there;
+}
+
+AttnSplit attn_few_split(const Geom& g, int nl, int n_total, size_t ws_bytes, int n_wgs) {
+  AttnSplit sp;
+  const int G = few_groups(g, nl, n_total, n_wgs);
+  sp.rows = G * kPartRows;
+  const long blocks = (long)((g.M + sp.rows - 1) / sp.rows) * g.H * nl;
+  long splits = few_splits(blocks, n_total, n_wgs);
+  while (splits > 1 && (size_t)(blocks * splits) * part_rec_floats(G) * sizeof(float) > ws_bytes) --splits;
+  sp.ranges = (int)splits;
+  sp.work = blocks * splits;
+  return sp;
 }
 
 hipError_t launch_attn_few(const Geom& g, char* kv, char* meta, int layer0, int nl, const void* q, void* out,
-                           int n_total, float scale, char* ws, size_t ws_bytes, bool out_f32, hipStream_t s) {
+                           int n_total, float scale, char* ws, size_t ws_bytes, int n_wgs, bool out_f32, hipStream_t s) {
   AttnFewParams p;
-  const int G = few_groups(g, nl, n_total);
+  const AttnSplit sp = attn_few_split(g, nl, n_total, ws_bytes, n_wgs);
   p.kv = kv; p.meta = meta; p.q = (const uint16_t*)q; p.out = (char*)out; p.recs = (float*)ws;
   p.layer0 = layer0; p.n_total = n_total;
-  p.QB = (g.M + G * kPartRows - 1) / (G * kPartRows);
+  p.QB = (g.M + sp.rows - 1) / sp.rows;
   const float c = fminf(scale * 1.4426950408889634f, 3.402823466e38f);
   p.q_limit = 65504.f / c;
   p.q_scale = ldexpf(1.0f, ilogbf(c));
   p.c = c / p.q_scale;
-  const long blocks = (long)p.QB * g.H * nl;
-  long splits = few_splits(blocks, n_total);
-  while (splits > 1 && (size_t)(blocks * splits) * part_rec_floats(G) * sizeof(float) > ws_bytes) --splits;
-  if (splits < 1) splits = 1;
-  p.splits = (int)splits;
-  const long work = blocks * splits;
-  if (work > 0x7FFFFFF0L) return hipErrorInvalidValue;
-  p.n_work = (int)work;
-  const dim3 grid((unsigned)((work + 7) / 8 * 8)), block(kPartThreads);
+  p.splits = sp.ranges;
+  if (sp.work > 0x7FFFFFF0L) return hipErrorInvalidValue;
+  p.n_work = (int)sp.work;
+  const dim3 grid((unsigned)((sp.work + 7) / 8 * 8)), block(kPartThreads);
 #define OVGGT_FEW_LAUNCH(GG) \
   if (out_f32) hipLaunchKernelGGL((attn_few_kernel<GG, true>), grid, block, 0, s, g, p); \
   else hipLaunchKernelGGL((attn_few_kernel<GG, false>), grid, block, 0, s, g, p)
-  switch (G) {
+  switch (sp.rows / kPartRows) {
     case 1: OVGGT_FEW_LAUNCH(1); break;
     case 2: OVGGT_FEW_LAUNCH(2); break;
     default: OVGGT_FEW_LAUNCH(4); break;

@@ -101,6 +101,9 @@ size_t ws_bytes_for(const ovggt_config& c) {
   return up256(one > all ? one : all);
 }
 
+// attention workgroups of a device of `cus` compute units
+int attn_wgs(int cus) { return std::clamp((std::min(cus, kMaxAttnWgs) + 7) & ~7, 8, kMaxAttnWgs); }
+
 bool aligned16(const void* p) { return p && ((uintptr_t)p & 15) == 0; }
 
 // resolves `layer` to [l0, l0+nl); false if out of range
@@ -211,11 +214,7 @@ int ovggt_cache_init(ovggt_cache** out, const ovggt_config* cfg, void* kv_dev, v
   for (int i = 0; i < 9; ++i) c->smooth.g[i] = cfg->smooth_kernel[i];
   c->kv = (char*)kv_dev; c->meta = (char*)meta_dev; c->ws = (char*)ws_dev;
   c->scale = cfg->softmax_scale > 0.f ? cfg->softmax_scale : 1.0f / std::sqrt((float)cfg->head_dim);
-  int wgs = cus;
-  wgs = (wgs + 7) & ~7;
-  if (wgs < 8) wgs = 8;
-  if (wgs > kMaxAttnWgs) wgs = kMaxAttnWgs;
-  c->n_wgs = wgs;
+  c->n_wgs = attn_wgs(cus);
   c->n.assign(c->g.L, 0);
   c->frames.assign(c->g.L, 0);
   c->phase.assign(c->g.L, 0);
@@ -278,10 +277,11 @@ static int global_attn_impl(ovggt_cache* c, int layer, const void* q, const void
         for (hipEvent_t x : ev)
           if (x) c->prof_free.push_back(x);
     }
-    if (attn_few_better(g, nl, n + g.M)) {                        // one kernel, merges included
+    if (attn_few_better(g, nl, n + g.M, c->n_wgs)) {                        // one kernel, merges included
       e = have ? hipEventRecord(ev[0], s) : hipSuccess;
       if (e == hipSuccess)
-        e = launch_attn_few(g, c->kv, c->meta, l0, nl, q, out, n + g.M, c->scale, ws, ws_bytes, c->cfg.out_dtype == OVGGT_F32, s);
+        e = launch_attn_few(g, c->kv, c->meta, l0, nl, q, out, n + g.M, c->scale, ws, ws_bytes, c->n_wgs,
+                            c->cfg.out_dtype == OVGGT_F32, s);
       for (int i = 1; i < 3 && have && e == hipSuccess; ++i) e = hipEventRecord(ev[i], s);
     } else {
       e = launch_attn_bf16(g, c->kv, l0, nl, q, out, n + g.M, c->scale, ws, ws_bytes, c->n_wgs,
@@ -293,7 +293,7 @@ static int global_attn_impl(ovggt_cache* c, int layer, const void* q, const void
     }
   } else {
     ProfScope ps(c, OVGGT_PROF_ATTN, s, prof_attn);
-    e = launch_attn_f32(g, c->kv, c->meta, l0, nl, q, out, n + g.M, c->scale, ws, ws_bytes, s);
+    e = launch_attn_f32(g, c->kv, c->meta, l0, nl, q, out, n + g.M, c->scale, ws, ws_bytes, c->n_wgs, s);
   }
   if (e != hipSuccess) return OVGGT_ERR_HIP;
   for (int l = l0; l < l0 + nl; ++l) { c->n[l] = n + g.M; c->phase[l] = 1; }
@@ -595,6 +595,24 @@ int ovggt_attn_plan_stats(const ovggt_config* cfg, int32_t layers_in_launch, int
   out[0] = st.n_wgs; out[1] = st.rounds; out[2] = st.segments; out[3] = st.balanced; out[4] = st.pieces_max;
   out[5] = st.tiles_min; out[6] = st.tiles_max; out[7] = st.shared_items;
   cost[0] = st.cost_max; cost[1] = st.cost_mean;
+  return OVGGT_OK;
+}
+
+int ovggt_attn_route(const ovggt_config* cfg, int32_t layers_in_launch, int32_t n_total, int32_t n_wgs, int32_t* out) {
+  if (!valid_config(cfg) || !out) return OVGGT_ERR_ARG;
+  if (layers_in_launch != 1 && layers_in_launch != cfg->n_layers) return OVGGT_ERR_ARG;
+  if (n_total < 1 || n_total > cfg->budget + cfg->tokens_per_frame || n_wgs < 1) return OVGGT_ERR_ARG;
+  Geom g;
+  make_geom(*cfg, &g);
+  n_wgs = attn_wgs(n_wgs);
+  const bool f32 = cfg->dtype == OVGGT_F32;
+  if (!f32 && !attn_few_better(g, layers_in_launch, n_total, n_wgs)) {
+    out[0] = OVGGT_ATTN_ITEMS; out[1] = kQueryTile; out[2] = 0; out[3] = n_wgs;
+    return OVGGT_OK;
+  }
+  const AttnSplit sp = (f32 ? attn_f32_split : attn_few_split)(g, layers_in_launch, n_total, ws_bytes_for(*cfg), n_wgs);
+  if (sp.work > 0x7FFFFFF0L) return OVGGT_ERR_STATE;
+  out[0] = f32 ? OVGGT_ATTN_F32 : OVGGT_ATTN_FEW; out[1] = sp.rows; out[2] = sp.ranges; out[3] = (int32_t)sp.work;
   return OVGGT_OK;
 }
 

@@ -80,14 +80,21 @@ hipError_t launch_spin(unsigned long long ticks, hipStream_t s);
 hipError_t launch_append(const Geom& g, char* kv, char* meta, int layer0, int nl,
                          const void* k_new, const void* v_new, int n, bool apply_moves, hipStream_t s);
 
-// Attention of M queries over n_total resident slots.
+// Attention of M queries over n_total resident slots.  n_wgs: the workgroups that fill the device, one
+// per compute unit (a multiple of 8, at most kMaxAttnWgs); every rule on how to cut a launch asks for it.
+struct AttnSplit {
+  int rows, ranges;          // queries of a workgroup; ranges of the slots, a workgroup for each
+  long work;                 // blocks of queries x ranges
+};
+AttnSplit attn_f32_split(const Geom& g, int nl, int n_total, size_t ws_bytes, int n_wgs);
 hipError_t launch_attn_f32(const Geom& g, char* kv, char* meta, int layer0, int nl, const void* q, void* out,
-                           int n_total, float scale, char* ws, size_t ws_bytes, hipStream_t s);
+                           int n_total, float scale, char* ws, size_t ws_bytes, int n_wgs, hipStream_t s);
 size_t attn_f32_ws_bytes(int layer_heads, int tokens_per_frame);
 // The same over the half-precision cache of bf16 handles, for launches that attn_few_better names.
 hipError_t launch_attn_few(const Geom& g, char* kv, char* meta, int layer0, int nl, const void* q, void* out,
-                           int n_total, float scale, char* ws, size_t ws_bytes, bool out_f32, hipStream_t s);
-bool attn_few_better(const Geom& g, int nl, int n_total);
+                           int n_total, float scale, char* ws, size_t ws_bytes, int n_wgs, bool out_f32, hipStream_t s);
+bool attn_few_better(const Geom& g, int nl, int n_total, int n_wgs);
+AttnSplit attn_few_split(const Geom& g, int nl, int n_total, size_t ws_bytes, int n_wgs);
 // `ev` (optional, 3 events) are recorded before the main kernel, between it and
 // the combine kernel, and after the combine kernel.
 hipError_t launch_attn_bf16(const Geom& g, char* kv, int layer0, int nl, const void* q, void* out,

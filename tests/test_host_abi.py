@@ -147,3 +147,28 @@ def test_attention_plans_cover_every_tile_once():
     assert B.ovggt_attn_plan_stats(B.make_config(1, 2, 64, 256, 64, 1000, "bf16"), 1, 1256, 256)["shared_items"] == 2
     assert B.ovggt_attn_plan_stats(B.make_config(1, 2, 64, 100, 64, 1000, "bf16"), 1, 1100, 256)["shared_items"] == 0
     print(st)
+
+
+def test_attention_route_follows_the_size_of_the_launch_and_of_the_device():
+    """Which kernel a launch takes and into how many ranges its slots are cut, on the host: small launches
+    are split until they fill the device they run on, and no further."""
+    route = lambda M, H, n, layers=1, dtype="bf16", n_wgs=256: B.ovggt_attn_route(
+        B.make_config(layers, H, 64, M, 64, max(n - M, M), dtype), layers, n, n_wgs)
+    assert route(1, 16, 189)["kernel"] == "few" and route(1374, 16, 17758)["kernel"] == "items"
+    assert route(65, 2, 321, dtype="f32") == {"kernel": "f32", "rows": 16, "ranges": 1, "workgroups": 10}
+    for dtype in ("bf16", "f32"):
+        for n_wgs in (32, 64, 128, 256):
+            for M, H, n in ((1, 1, 5000), (1, 16, 4097), (65, 2, 4161), (17, 8, 1017), (130, 1, 9000)):
+                r = route(M, H, n, dtype=dtype, n_wgs=n_wgs)
+                blocks = -(-M // r["rows"]) * H
+                if r["kernel"] == "items":
+                    continue
+                assert r["workgroups"] == blocks * r["ranges"] <= max(blocks, n_wgs), (dtype, n_wgs, M, H, n, r)
+                assert r["ranges"] == 1 or blocks < n_wgs
+    # more blocks than compute units: ranges even out the last round of the device at hand
+    assert route(272, 16, 1572, dtype="f32")["ranges"] == 1 and route(1041, 16, 5137, dtype="f32")["ranges"] > 1
+    cfg = B.make_config(2, 16, 64, 65, 64, 4096, "bf16")
+    for bad in ((3, 100, 256), (1, 0, 256), (1, 5000, 256), (1, 100, 0)):
+        with pytest.raises(B.OvggtError) as e:
+            B.ovggt_attn_route(cfg, *bad)
+        assert e.value.code == B.OVGGT_ERR_ARG
