@@ -312,7 +312,8 @@ int ovggt_dap_destroy(ovggt_dap* d);
  * kernel: work items of 128 queries and a merge pass (OVGGT_ATTN_ITEMS, see ovggt_attn_plan_stats),
  * the one for small launches (OVGGT_ATTN_FEW) or the fp32 one; out[1] = queries of a workgroup at a
  * time; out[2] = ranges that the slots are cut into, a workgroup for each (0 for OVGGT_ATTN_ITEMS);
- * out[3] = workgroups.  OVGGT_OK, ERR_ARG (bad config or sizes), ERR_STATE (more workgroups than a
+ * out[3] = workgroups; out[4..5] = the grid's columns and rows of workgroups (512 threads each), which
+ * hold at least as many.  OVGGT_OK, ERR_ARG (bad config or sizes), ERR_STATE (more workgroups than a
  * launch may have). */
 enum { OVGGT_ATTN_ITEMS = 0, OVGGT_ATTN_FEW = 1, OVGGT_ATTN_F32 = 2 };
 int ovggt_attn_route(const ovggt_config* cfg, int32_t layers_in_launch, int32_t n_total, int32_t n_wgs, int32_t* out);

@@ -252,9 +252,10 @@ def ovggt_attn_plan_stats(cfg: ovggt_config, layers_in_launch: int, n_total: int
 
 
 def ovggt_attn_route(cfg: ovggt_config, layers_in_launch: int, n_total: int, n_wgs: int = 256) -> dict:
-    out = (C.c_int32 * 4)()
+    out = (C.c_int32 * 6)()
     _check(lib().ovggt_attn_route(C.byref(cfg), layers_in_launch, n_total, n_wgs, out), "ovggt_attn_route")
-    return {"kernel": ATTN_KERNELS[out[0]], "rows": out[1], "ranges": out[2], "workgroups": out[3]}
+    return {"kernel": ATTN_KERNELS[out[0]], "rows": out[1], "ranges": out[2], "workgroups": out[3],
+            "grid": (out[4], out[5])}
 
 
 def ovggt_profile_enable(h, level: int, every: int = 1) -> None:

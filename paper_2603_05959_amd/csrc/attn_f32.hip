@@ -52,7 +52,8 @@ attn_f32_kernel(Geom g, AttnF32Params p) {
   __shared__ MergeArea<1> area;
   // Consecutive workgroups of an XCD walk the query blocks of one range of one head, whose K and V
   // rows then come from that XCD's L2.
-  const int idx = (int)(blockIdx.x & 7) * (int)(gridDim.x >> 3) + (int)(blockIdx.x >> 3);
+  const unsigned wg = blockIdx.y * gridDim.x + blockIdx.x;
+  const int idx = (int)((wg & 7) * (gridDim.x >> 3) * gridDim.y + (wg >> 3));
   if (idx >= p.n_work) return;                                       // whole workgroup
   const int qb = idx % p.QB, rest = idx / p.QB;
   const int sp = rest % p.splits, lh = rest / p.splits;
@@ -176,6 +177,15 @@ AttnSplit attn_f32_split(const Geom& g, int nl, int n_total, size_t ws_bytes, in
   return sp;
 }
 
+// A launch takes less than 2^32 threads along x: beyond 2^22 workgroups (of 512) the grid gets rows.
+bool attn_f32_grid(long work, unsigned* x, unsigned* y) {
+  constexpr long kMaxX = 1L << 22;
+  const long rows = (work + kMaxX - 1) / kMaxX, wide = ((work + rows - 1) / rows + 7) / 8 * 8;      // whole rounds of the 8 XCDs
+  if (rows * wide > 0x7FFFFFFFL) return false;
+  *x = (unsigned)wide; *y = (unsigned)rows;
+  return true;
+}
+
 hipError_t launch_attn_f32(const Geom& g, char* kv, char* meta, int layer0, int nl, const void* q, void* out,
                            int n_total, float scale, char* ws, size_t ws_bytes, int n_wgs, hipStream_t s) {
   AttnF32Params p;
@@ -186,9 +196,10 @@ hipError_t launch_attn_f32(const Geom& g, char* kv, char* meta, int layer0, int 
   p.QB = (g.M + kF32Rows - 1) / kF32Rows;
   p.c = scale * 1.4426950408889634f;
   p.splits = sp.ranges;
-  if (sp.work > 0x7FFFFFF0L) return hipErrorInvalidValue;
+  unsigned gx, gy;
+  if (!attn_f32_grid(sp.work, &gx, &gy)) return hipErrorInvalidValue;
   p.n_work = (int)sp.work;
-  hipLaunchKernelGGL(attn_f32_kernel, dim3((unsigned)((sp.work + 7) / 8 * 8)), dim3(kPartThreads), 0, s, g, p);
+  hipLaunchKernelGGL(attn_f32_kernel, dim3(gx, gy), dim3(kPartThreads), 0, s, g, p);
   return hipGetLastError();
 }
 

@@ -607,11 +607,13 @@ int ovggt_attn_route(const ovggt_config* cfg, int32_t layers_in_launch, int32_t 
   n_wgs = attn_wgs(n_wgs);
   const bool f32 = cfg->dtype == OVGGT_F32;
   if (!f32 && !attn_few_better(g, layers_in_launch, n_total, n_wgs)) {
-    out[0] = OVGGT_ATTN_ITEMS; out[1] = kQueryTile; out[2] = 0; out[3] = n_wgs;
+    out[0] = OVGGT_ATTN_ITEMS; out[1] = kQueryTile; out[2] = 0; out[3] = out[4] = n_wgs; out[5] = 1;
     return OVGGT_OK;
   }
   const AttnSplit sp = (f32 ? attn_f32_split : attn_few_split)(g, layers_in_launch, n_total, ws_bytes_for(*cfg), n_wgs);
-  if (sp.work > 0x7FFFFFF0L) return OVGGT_ERR_STATE;
+  unsigned gx = (unsigned)((sp.work + 7) / 8 * 8), gy = 1;
+  if (sp.work > 0x7FFFFFF0L || (f32 && !attn_f32_grid(sp.work, &gx, &gy))) return OVGGT_ERR_STATE;
+  out[4] = (int32_t)gx; out[5] = (int32_t)gy;
   out[0] = f32 ? OVGGT_ATTN_F32 : OVGGT_ATTN_FEW; out[1] = sp.rows; out[2] = sp.ranges; out[3] = (int32_t)sp.work;
   return OVGGT_OK;
 }

@@ -87,6 +87,7 @@ struct AttnSplit {
   long work;                 // blocks of queries x ranges
 };
 AttnSplit attn_f32_split(const Geom& g, int nl, int n_total, size_t ws_bytes, int n_wgs);
+bool attn_f32_grid(long work, unsigned* x, unsigned* y);
 hipError_t launch_attn_f32(const Geom& g, char* kv, char* meta, int layer0, int nl, const void* q, void* out,
                            int n_total, float scale, char* ws, size_t ws_bytes, int n_wgs, hipStream_t s);
 size_t attn_f32_ws_bytes(int layer_heads, int tokens_per_frame);

@@ -155,7 +155,7 @@ def test_attention_route_follows_the_size_of_the_launch_and_of_the_device():
     route = lambda M, H, n, layers=1, dtype="bf16", n_wgs=256: B.ovggt_attn_route(
         B.make_config(layers, H, 64, M, 64, max(n - M, M), dtype), layers, n, n_wgs)
     assert route(1, 16, 189)["kernel"] == "few" and route(1374, 16, 17758)["kernel"] == "items"
-    assert route(65, 2, 321, dtype="f32") == {"kernel": "f32", "rows": 16, "ranges": 1, "workgroups": 10}
+    assert route(65, 2, 321, dtype="f32") == {"kernel": "f32", "rows": 16, "ranges": 1, "workgroups": 10, "grid": (16, 1)}
     for dtype in ("bf16", "f32"):
         for n_wgs in (32, 64, 128, 256):
             for M, H, n in ((1, 1, 5000), (1, 16, 4097), (65, 2, 4161), (17, 8, 1017), (130, 1, 9000)):
@@ -172,3 +172,18 @@ def test_attention_route_follows_the_size_of_the_launch_and_of_the_device():
         with pytest.raises(B.OvggtError) as e:
             B.ovggt_attn_route(cfg, *bad)
         assert e.value.code == B.OVGGT_ERR_ARG
+
+
+@pytest.mark.parametrize("layers,M,H", [(1, 1, 1), (24, 1041, 16), (1, 65536, 1024), (4096, 49, 512), (4096, 49, 600), (4096, 16, 1024)])
+def test_fp32_attention_grids_stay_within_a_launch(layers, M, H):
+    """The largest stacks of short caches that 288 GB hold have more than 2^23 blocks of queries: fewer
+    than 2^32 threads along x, whole rounds of the 8 XCDs, every block in the grid once."""
+    cfg = B.make_config(layers, H, 64, M, 1, M if M > 64 else 64, "f32")
+    r = B.ovggt_attn_route(cfg, layers, M)
+    x, y = r["grid"]
+    assert r["workgroups"] >= layers * H * -(-M // 16)
+    assert x % 8 == 0 and x * 512 < 2 ** 32 and y < 65536
+    assert r["workgroups"] <= x * y < min(r["workgroups"] + 8 * y, 2 ** 31)
+    if x * y < 1 << 16:                                 # the kernel's numbering, over the whole grid
+        seen = sorted((wg & 7) * (x >> 3) * y + (wg >> 3) for wg in range(x * y))
+        assert seen == list(range(x * y))
