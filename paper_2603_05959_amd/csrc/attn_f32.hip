@@ -21,7 +21,9 @@
 
 namespace ovggt {
 
-constexpr float kF32Lag = 8.0f;         // the softmax reference may lag the running maximum by 2^8
+constexpr float kF32Lag = 8.0f;         // the softmax reference may lag the running maximum by 2^8: the largest weight
+constexpr float kF32Low = -24.0f;       // the same of a wave that starts over
+constexpr float kF32Far = 0x1p100f;     // weighted sums up to here stay finite when 8 waves of 16 ranges are merged
 constexpr int kF32Rows = kPartRows;     // queries of a workgroup
 constexpr int kF32MaxRecs = 4096;       // parts of a split launch (17 MB of workspace at most)
 
@@ -74,66 +76,81 @@ attn_f32_kernel(Geom g, AttnF32Params p) {
   const int t0 = (int)((long)nt * sp / p.splits), t1 = (int)((long)nt * (sp + 1) / p.splits);
   const bool ragged = (n_total & 15) != 0;
   const float c = p.c;
-  f32x4 kf[4], vf[4], O[1][4];
-  float m[1] = {-3.402823466e38f}, l[1] = {0.f};
+  f32x4 O[1][4];
+  float m[1], l[1];
+  auto walk = [&](const float top) {                     // top: the largest weight, as a power of two
+    f32x4 kf[4], vf[4];
+    m[0] = -3.402823466e38f;
+    l[0] = 0.f;
 #pragma unroll
-  for (int d = 0; d < 4; ++d) O[0][d] = f32x4{0.f, 0.f, 0.f, 0.f};
-  // rows at or beyond n_total are never read (they may hold anything): the last resident row stands in
-  auto load_k = [&](int t) {
-    const float* kp = kbase + (size_t)min(t * 16 + l16, n_total - 1) * 64 + 4 * gl;
+    for (int d = 0; d < 4; ++d) O[0][d] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // rows at or beyond n_total are never read (they may hold anything): the last resident row stands in
+    auto load_k = [&](int t) {
+      const float* kp = kbase + (size_t)min(t * 16 + l16, n_total - 1) * 64 + 4 * gl;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) kf[j] = *(const f32x4*)(kp + 16 * j);
-  };
-  auto load_v = [&](int t) {
+      for (int j = 0; j < 4; ++j) kf[j] = *(const f32x4*)(kp + 16 * j);
+    };
+    auto load_v = [&](int t) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-      vf[i] = *(const f32x4*)(vbase + (size_t)min(t * 16 + 4 * gl + i, n_total - 1) * 64 + 4 * l16);
-  };
-  if (t0 + wave < t1) { load_k(t0 + wave); load_v(t0 + wave); }
-  for (int t = t0 + wave; t < t1; t += W) {
-    const int tn = min(t + W, t1 - 1);
-    f32x4 S;
-    {
-      f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0;        // two chains: a product never waits for the one before it
+      for (int i = 0; i < 4; ++i)
+        vf[i] = *(const f32x4*)(vbase + (size_t)min(t * 16 + 4 * gl + i, n_total - 1) * 64 + 4 * l16);
+    };
+    if (t0 + wave < t1) { load_k(t0 + wave); load_v(t0 + wave); }
+    for (int t = t0 + wave; t < t1; t += W) {
+      const int tn = min(t + W, t1 - 1);
+      f32x4 S;
+      {
+        f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0;        // two chains: a product never waits for the one before it
 #pragma unroll
-      for (int e = 0; e < 4; ++e)
+        for (int e = 0; e < 4; ++e)
 #pragma unroll
-        for (int j = 0; j < 4; j += 2) {
-          s0 = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[j][e], qf[j][e], s0, 0, 0, 0);
-          s1 = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[j + 1][e], qf[j + 1][e], s1, 0, 0, 0);
-        }
-      S = s0 + s1;
-    }
-    load_k(tn);                                        // K of the next tile travels during this tile's P V, V during its Q K
-    if (ragged && t == nt - 1) {                       // absent slots: no weight, and no 0 * inf from the stand-in row
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const bool absent = t * 16 + 4 * gl + i >= n_total;
-        S[i] = absent ? -INFINITY : S[i];
-        if (absent) vf[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+          for (int j = 0; j < 4; j += 2) {
+            s0 = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[j][e], qf[j][e], s0, 0, 0, 0);
+            s1 = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[j + 1][e], qf[j + 1][e], s1, 0, 0, 0);
+          }
+        S = s0 + s1;
       }
+      load_k(tn);                                        // K of the next tile travels during this tile's P V, V during its Q K
+      if (ragged && t == nt - 1) {                       // absent slots: no weight, and no 0 * inf from the stand-in row
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const bool absent = t * 16 + 4 * gl + i >= n_total;
+          S[i] = absent ? -INFINITY : S[i];
+          if (absent) vf[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+      }
+      // The reference m follows the maximum only when it is passed by 2^8 (weights are fp32: no
+      // accuracy is lost), so most tiles rescale nothing and look at no other lane.
+      const float mx = fmaxf(fmaxf(S[0], S[1]), fmaxf(S[2], S[3])) * c;
+      if (__builtin_amdgcn_ballot_w64(mx > m[0] + top) != 0ull) {
+        float x = fmaxf(mx, __shfl_xor(mx, 16, 64));
+        x = fmaxf(x, __shfl_xor(x, 32, 64));
+        const float mn = fmaxf(m[0], x - fminf(top, 0.f)), a = __builtin_amdgcn_exp2f(m[0] - mn);
+        m[0] = mn;
+        l[0] *= a;
+#pragma unroll
+        for (int d = 0; d < 4; ++d) O[0][d] *= a;
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) S[i] = __builtin_amdgcn_exp2f(fmaf(S[i], c, -m[0]));
+      l[0] += (S[0] + S[1]) + (S[2] + S[3]);
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int d = 0; d < 4; ++d) O[0][d] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[i][d], S[i], O[0][d], 0, 0, 0);
+      load_v(tn);
     }
-    // The reference m follows the maximum only when it is passed by 2^8 (weights are fp32: no
-    // accuracy is lost), so most tiles rescale nothing and look at no other lane.
-    const float mx = fmaxf(fmaxf(S[0], S[1]), fmaxf(S[2], S[3])) * c;
-    if (__builtin_amdgcn_ballot_w64(mx > m[0] + kF32Lag) != 0ull) {
-      float x = fmaxf(mx, __shfl_xor(mx, 16, 64));
-      x = fmaxf(x, __shfl_xor(x, 32, 64));
-      const float mn = fmaxf(m[0], x), a = __builtin_amdgcn_exp2f(m[0] - mn);
-      m[0] = mn;
-      l[0] *= a;
+  };
+  walk(kF32Lag);
+  // Sums of weights up to 2^8, or of many weights of 1 that turn out to be small beside another wave's, leave the
+  // fp32 range where values of V are near its end, although the result, a mean of them, does not.  Such a wave
+  // starts over with weights up to 2^-24: 2^17 slots of any value stay below the largest number.
+  bool far = false;
 #pragma unroll
-      for (int d = 0; d < 4; ++d) O[0][d] *= a;
-    }
+  for (int d = 0; d < 4; ++d)
 #pragma unroll
-    for (int i = 0; i < 4; ++i) S[i] = __builtin_amdgcn_exp2f(fmaf(S[i], c, -m[0]));
-    l[0] += (S[0] + S[1]) + (S[2] + S[3]);
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int d = 0; d < 4; ++d) O[0][d] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[i][d], S[i], O[0][d], 0, 0, 0);
-    load_v(tn);
-  }
+    for (int i = 0; i < 4; ++i) far = far || !(fabsf(O[0][d][i]) <= kF32Far);
+  if (__builtin_amdgcn_ballot_w64(far) != 0ull) walk(kF32Low);
 
   l[0] += __shfl_xor(l[0], 16, 64);
   l[0] += __shfl_xor(l[0], 32, 64);

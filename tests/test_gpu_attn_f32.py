@@ -64,3 +64,37 @@ def test_rows_behind_the_last_slot_are_not_read():
     cache.step(q.cuda(), k.cuda(), v.cuda(), torch.ones(1, M, 64).cuda(), None, out)
     assert torch.isfinite(out).all()
     cache.close()
+
+
+@pytest.mark.parametrize("n_old,H,layers", [(700, 1, 1), (4000, 2, 1), (300, 16, 24)])   # split into ranges, and not
+def test_values_near_the_ends_of_the_fp32_range(n_old, H, layers):
+    """Logits that rise slowly enough for the softmax reference to stay behind, and many slots of almost no
+    weight, over values of V near the largest fp32 number: the result is a mean of them and finite.  And values
+    near the smallest one."""
+    import torch
+    M = 3
+    for size in (1e38, 1e-36):
+        cache = B.Cache(layers, H, 64, M, 64, n_old, "f32")
+        gen = torch.Generator().manual_seed(n_old)
+        n = n_old + M
+        # every 32nd slot is one of the rising ones (from e^-6 to 1); between them the weights are e^-60 and less
+        logit = torch.full((n,), -60.0)
+        logit[::32] = torch.linspace(-6.0, 0.0, len(logit[::32]))
+        k = torch.zeros(layers, n, H, 64)
+        k[..., 0] = logit[None, :, None] * 8.0
+        v = (0.5 + torch.rand(layers, n, H, 64, generator=gen)) * size * torch.where(torch.rand(64, generator=gen) < 0.5, -1.0, 1.0)
+        v /= torch.softmax(logit.double(), 0).max().reciprocal().float()      # sums of weighted values stay finite, too
+        for l in range(layers):
+            cache.import_(l, 3 + n_old // M, np.arange(n_old, dtype=np.uint32), k[l, :n_old].numpy(), v[l, :n_old].numpy(),
+                          np.ones(n_old, np.float32), np.zeros(n_old, np.uint8))
+        q = torch.zeros(layers, M, H, 64)
+        q[..., 0] = 1.0
+        out = cache.new_output()
+        cache.step(q.cuda(), k[:, n_old:].contiguous().cuda(), v[:, n_old:].contiguous().cuda(), torch.ones(layers, M, 64, device="cuda"), None, out)
+        got = out.cpu().double()
+        p = torch.softmax(logit.double(), 0)
+        ref = torch.matmul(p, v.double().permute(0, 2, 1, 3)).unsqueeze(1)
+        assert torch.isfinite(got).all()
+        # sixty-four roundings of 2^-24 in a score of size 60, as above; few of them where the weight is
+        assert (got - ref).norm() / (ref.norm() * M ** 0.5) < 5e-6, size
+        cache.close()
