@@ -18,12 +18,15 @@
 // 32 queries halve that traffic but fill the chip worse (528 instead of 1056 blocks
 // for 256 CUs) and took 10 to 20 % longer over every size from 17 to 1041 queries.
 #include "attn_parts.h"
+#include <type_traits>
 
 namespace ovggt {
 
-constexpr float kF32Lag = 8.0f;         // the softmax reference may lag the running maximum by 2^8: the largest weight
-constexpr float kF32Low = -24.0f;       // the same of a wave that starts over
+constexpr float kF32Lag = 8.0f;         // the softmax reference may lag the running maximum by 2^8
+constexpr int kF32Unit = 4;             // exponents of a wave that starts over, and of the merge, count powers of 2^4
+constexpr float kF32Low = 6.0f;         // how far, in these, its reference lies above the maximum
 constexpr float kF32Far = 0x1p100f;     // weighted sums up to here stay finite when 8 waves of 16 ranges are merged
+constexpr float kF32High = 0x1p24f;     // exponents of the first walk are within 1 of the true ones up to here
 constexpr int kF32Rows = kPartRows;     // queries of a workgroup
 constexpr int kF32MaxRecs = 4096;       // parts of a split launch (17 MB of workspace at most)
 
@@ -41,7 +44,7 @@ struct AttnF32Params {
   float* out;
   float* recs;
   int layer0, n_total, QB, n_work, splits;
-  float c;                    // softmax scale * log2(e)
+  float c, c_unit;            // softmax scale * log2(e), and the same over kF32Unit
 };
 
 // A workgroup takes 16 queries of one head over one of `splits` equal ranges of
@@ -75,10 +78,11 @@ attn_f32_kernel(Geom g, AttnF32Params p) {
   const int n_total = p.n_total, nt = (n_total + 15) >> 4;
   const int t0 = (int)((long)nt * sp / p.splits), t1 = (int)((long)nt * (sp + 1) / p.splits);
   const bool ragged = (n_total & 15) != 0;
-  const float c = p.c;
   f32x4 O[1][4];
   float m[1], l[1];
-  auto walk = [&](const float top) {                     // top: the largest weight, as a power of two
+  auto walk = [&](auto second) {
+    constexpr bool over = decltype(second)::value;
+    const float c = over ? p.c_unit : p.c;
     f32x4 kf[4], vf[4];
     m[0] = -3.402823466e38f;
     l[0] = 0.f;
@@ -122,17 +126,17 @@ attn_f32_kernel(Geom g, AttnF32Params p) {
       // The reference m follows the maximum only when it is passed by 2^8 (weights are fp32: no
       // accuracy is lost), so most tiles rescale nothing and look at no other lane.
       const float mx = fmaxf(fmaxf(S[0], S[1]), fmaxf(S[2], S[3])) * c;
-      if (__builtin_amdgcn_ballot_w64(mx > m[0] + top) != 0ull) {
+      if (__builtin_amdgcn_ballot_w64(mx > m[0] + (over ? -kF32Low : kF32Lag)) != 0ull) {
         float x = fmaxf(mx, __shfl_xor(mx, 16, 64));
         x = fmaxf(x, __shfl_xor(x, 32, 64));
-        const float mn = fmaxf(m[0], x - fminf(top, 0.f)), a = __builtin_amdgcn_exp2f(m[0] - mn);
+        const float mn = fmaxf(m[0], over ? x + kF32Low : x), a = __builtin_amdgcn_exp2f((over ? kF32Unit : 1) * (m[0] - mn));
         m[0] = mn;
         l[0] *= a;
 #pragma unroll
         for (int d = 0; d < 4; ++d) O[0][d] *= a;
       }
 #pragma unroll
-      for (int i = 0; i < 4; ++i) S[i] = __builtin_amdgcn_exp2f(fmaf(S[i], c, -m[0]));
+      for (int i = 0; i < 4; ++i) S[i] = __builtin_amdgcn_exp2f(over ? kF32Unit * (S[i] * c - m[0]) : fmaf(S[i], c, -m[0]));
       l[0] += (S[0] + S[1]) + (S[2] + S[3]);
 #pragma unroll
       for (int i = 0; i < 4; ++i)
@@ -141,22 +145,27 @@ attn_f32_kernel(Geom g, AttnF32Params p) {
       load_v(tn);
     }
   };
-  walk(kF32Lag);
-  // Sums of weights up to 2^8, or of many weights of 1 that turn out to be small beside another wave's, leave the
-  // fp32 range where values of V are near its end, although the result, a mean of them, does not.  Such a wave
-  // starts over with weights up to 2^-24: 2^17 slots of any value stay below the largest number.
-  bool far = false;
+  walk(std::false_type());
+  // Where the first walk does not hold, the wave starts over.
+  // Scores times c leave the fp32 range where scores times the scale do not, and above 2^24 what a fused exponent
+  // leaves of the largest score's rounding is no longer small: exponents in units of 2^4, rounded before the reference
+  // is taken off, count every score that is finite once scaled.
+  // Sums of weights up to 2^8, or of many weights of 1 that turn out to be small beside another wave's, leave the fp32
+  // range where values of V are near its end, although the result, a mean of them, does not: with weights up to
+  // 2^-24, 2^17 slots of any value stay below the largest number.
+  float size = 0.f;                                      // infinities and NaN stay in it
 #pragma unroll
   for (int d = 0; d < 4; ++d)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) far = far || !(fabsf(O[0][d][i]) <= kF32Far);
-  if (__builtin_amdgcn_ballot_w64(far) != 0ull) walk(kF32Low);
+    size += (fabsf(O[0][d][0]) + fabsf(O[0][d][1])) + (fabsf(O[0][d][2]) + fabsf(O[0][d][3]));
+  const bool far = !(size <= kF32Far) || !(fabsf(m[0]) <= kF32High);     // a wave without tiles, too: its m stays the lowest
+  if (__builtin_amdgcn_ballot_w64(far) != 0ull) walk(std::true_type());
+  else m[0] *= 1.0f / kF32Unit;
 
   l[0] += __shfl_xor(l[0], 16, 64);
   l[0] += __shfl_xor(l[0], 32, 64);
   uint32_t* arrive = (uint32_t*)(layer_meta(p.meta, g, p.layer0 + li) + g.off_arrive) + (size_t)h * p.QB + qb;
   const size_t first = (size_t)lh * p.splits * p.QB + qb;              // record of range 0; the ranges are QB apart
-  merge_and_write(area, O, m, l, sp, p.splits, arrive, p.recs + first * part_rec_floats(1), (size_t)p.QB * part_rec_floats(1),
+  merge_and_write<kF32Unit>(area, O, m, l, sp, p.splits, arrive, p.recs + first * part_rec_floats(1), (size_t)p.QB * part_rec_floats(1),
                      [&](int row, int piece, const f32x4& r) {
                        if (q0 + row < g.M) *(f32x4*)(p.out + (((size_t)li * g.M + q0 + row) * g.H + h) * 64 + 4 * piece) = r;
                      });
@@ -212,6 +221,7 @@ hipError_t launch_attn_f32(const Geom& g, char* kv, char* meta, int layer0, int 
   p.layer0 = layer0; p.n_total = n_total;
   p.QB = (g.M + kF32Rows - 1) / kF32Rows;
   p.c = scale * 1.4426950408889634f;
+  p.c_unit = (scale / kF32Unit) * 1.4426950408889634f;
   p.splits = sp.ranges;
   unsigned gx, gy;
   if (!attn_f32_grid(sp.work, &gx, &gy)) return hipErrorInvalidValue;

@@ -173,7 +173,7 @@ attn_few_kernel(Geom g, AttnFewParams p) {
   uint32_t* arrive = (uint32_t*)(layer_meta(p.meta, g, p.layer0 + li) + g.off_arrive) + (size_t)h * p.QB + qb;
   constexpr int rec = part_rec_floats(G);
   const size_t first = (size_t)lh * p.splits * p.QB + qb;              // record of range 0; the ranges are QB apart
-  merge_and_write(area, O, m, l, sp, p.splits, arrive, p.recs + first * rec, (size_t)p.QB * rec,
+  merge_and_write<1>(area, O, m, l, sp, p.splits, arrive, p.recs + first * rec, (size_t)p.QB * rec,
                      [&](int row, int piece, const f32x4& r) {
                        if (q0 + row >= g.M) return;
                        const size_t at = (((size_t)li * g.M + q0 + row) * g.H + h) * 64 + 4 * piece;

@@ -33,9 +33,9 @@ __device__ inline void store_through(float* p, const f32x4& v) {
 // Each of the 8 waves holds, for G groups of 16 queries, unnormalised O^T (lane (l16, gl), accumulator d,
 // element i: query l16, output element 16 gl + 4 i + d), the softmax reference m and the weight sum l of
 // query l16 (the same in all four gl).  `write(row, piece, o)` receives the normalised elements 4 piece .. +3 of
-// query `row` (0 .. 16 G - 1) of the block.  With splits > 1 the parts of the block are records at
+// query `row` (0 .. 16 G - 1) of the block.  References count powers of 2^UNIT.  With splits > 1 the parts of the block are records at
 // recs + s * rec_stride, counted at `arrive` (zero before and after); the last arrival merges them.
-template <int G, int N, typename Write>
+template <int UNIT, int G, int N, typename Write>
 __device__ inline void merge_and_write(MergeArea<N>& a, const f32x4 (&O)[G][4], const float (&m)[G], const float (&l)[G], int sp,
                                        int splits, uint32_t* arrive, float* recs, size_t rec_stride, Write write) {
   static_assert(G % N == 0 && N <= 2, "32 rows of 16 pieces a pass");
@@ -53,7 +53,7 @@ __device__ inline void merge_and_write(MergeArea<N>& a, const f32x4 (&O)[G][4], 
       float mt = a.m[q][0][l16];
 #pragma unroll
       for (int w = 1; w < kPartWaves; ++w) mt = fmaxf(mt, a.m[q][w][l16]);
-      const float f = __builtin_amdgcn_exp2f(m[q0 + q] - mt);
+      const float f = __builtin_amdgcn_exp2f(UNIT * (m[q0 + q] - mt));
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const f32x4 o = {O[q0 + q][0][i] * f, O[q0 + q][1][i] * f, O[q0 + q][2][i] * f, O[q0 + q][3][i] * f};
@@ -69,7 +69,7 @@ __device__ inline void merge_and_write(MergeArea<N>& a, const f32x4 (&O)[G][4], 
       for (int w = 1; w < kPartWaves; ++w) mt = fmaxf(mt, a.m[q][w][r16]);
 #pragma unroll
       for (int w = 0; w < kPartWaves; ++w) {
-        ls += a.l[q][w][r16] * __builtin_amdgcn_exp2f(a.m[q][w][r16] - mt);
+        ls += a.l[q][w][r16] * __builtin_amdgcn_exp2f(UNIT * (a.m[q][w][r16] - mt));
         o += *(const f32x4*)&a.o[q][w][r16][4 * piece];
       }
       const int r = q0 * kPartRows + row;
@@ -113,7 +113,7 @@ __device__ inline void merge_and_write(MergeArea<N>& a, const f32x4 (&O)[G][4], 
     for (int s = 0; s < kMaxSplits; ++s) mt = fmaxf(mt, pm[s]);
 #pragma unroll
     for (int s = 0; s < kMaxSplits; ++s) {
-      pm[s] = s < splits ? __builtin_amdgcn_exp2f(pm[s] - mt) : 0.f;
+      pm[s] = s < splits ? __builtin_amdgcn_exp2f(UNIT * (pm[s] - mt)) : 0.f;
       ls += s < splits ? pl[s] * pm[s] : 0.f;
     }
     f32x4 o = {0.f, 0.f, 0.f, 0.f};

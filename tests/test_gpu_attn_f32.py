@@ -98,3 +98,30 @@ def test_values_near_the_ends_of_the_fp32_range(n_old, H, layers):
         # sixty-four roundings of 2^-24 in a score of size 60, as above; few of them where the weight is
         assert (got - ref).norm() / (ref.norm() * M ** 0.5) < 5e-6, size
         cache.close()
+
+
+@pytest.mark.parametrize("scale,q0,k0", [(3e38, 0.0, 1.0), (2.5e38, 4e-19, 4e-19), (1.0, 1.2e19, 2e19), (0.5, 1.2e19, 2e19), (0.0, 3e5, 7e5),
+                                         (2.0, 1.0, 3.0)])
+@pytest.mark.parametrize("M,n_old", [(5, 90), (17, 3000)])       # one range of the slots, and several
+def test_scores_up_to_the_end_of_the_fp32_range(scale, q0, k0, M, n_old):
+    """Every finite softmax scale is accepted, and every score counts that is finite once scaled."""
+    import torch
+    H, n = 2, n_old + M
+    cache = B.Cache(1, H, 64, M, 64, n_old, "f32", softmax_scale=scale)
+    gen = torch.Generator().manual_seed(M)
+    k, v = torch.zeros(n, H, 64), torch.randn(n, H, 64, generator=gen)
+    k[:, :, 3] = k0 * torch.randint(0, 4, (n, 1), generator=gen) / 3.0        # four sizes of score: ties at the top
+    q = torch.zeros(1, M, H, 64)
+    q[..., 3] = q0
+    cache.import_(0, 3 + n_old // M, np.arange(n_old, dtype=np.uint32), k[:n_old].numpy(), v[:n_old].numpy(),
+                  np.ones(n_old, np.float32), np.zeros(n_old, np.uint8))
+    out = cache.new_output()
+    cache.step(q.cuda(), k[None, n_old:].contiguous().cuda(), v[None, n_old:].contiguous().cuda(),
+               torch.ones(1, M, 64, device="cuda"), None, out)
+    s = q[0, 0, 0, 3].double() * k[:, 0, 3].double() * float(np.float32(scale or 0.125))
+    assert s.abs().max() < 3.4e38
+    ref = torch.einsum("n,nhd->hd", torch.softmax(s, 0), v.double())
+    got = out[0].cpu().double()
+    # scores are equal, too far apart for more than one group to count, or at most 40 with errors of a few 2^-24 of that
+    assert ((got - ref).norm(dim=(1, 2)) / ref.norm() < 5e-6).all(), (got - ref).abs().max()
+    cache.close()
