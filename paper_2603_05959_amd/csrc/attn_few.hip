@@ -197,17 +197,20 @@ static long few_splits(long blocks, int n_total, int cus) {
   return s > kMaxSplits ? kMaxSplits : s;
 }
 
-// What a launch with G groups of 16 queries a workgroup takes beside its fixed part, in us: what the larger
-// merge adds, then the rate at which 256 CUs take 16 queries past a slot (fit over 1 to 1041 queries, 600 to 65 K
-// slots, 2 to 192 heads: 51 million such units take 1060 us with G = 1, 545 with 2 and 330 with 4), over the share of
-// the CUs that the last round of workgroups fills (520 queries of 16 heads over 2568 slots, 272 workgroups with
-// G = 2: 51.6 us, the time of 512).
+// What a launch with G groups of 16 queries a workgroup takes beyond the fixed part of the smallest, in us: what the
+// larger merge adds, what each round of workgroups after the first adds (first loads and merge of the waves), what the
+// merge of ranges adds, and the rate at which 256 CUs take 16 queries past a slot, over the share of the CUs that the
+// rounds fill.  Fit over 590 launches of 1 to 2100 queries, 16 to 32 K slots and 1 to 2304 heads, all three G: 5 to 6 %
+// rms.  Without the part for further rounds 226 queries over 573 slots of 2304 heads, 36 rounds of 13 us, counted as one.
 static float few_cost(int G, const Geom& g, int nl, int n_total, int cus) {
-  const long blocks = (long)((g.M + G * kPartRows - 1) / (G * kPartRows)) * g.H * nl;
-  const float extra = G == 1 ? 0.f : G == 2 ? 2.f : 8.f, rate = G == 1 ? 20.8e-6f : G == 2 ? 11.5e-6f : 7.0e-6f;
-  const long wgs = blocks * few_splits(blocks, n_total, cus), rounds = (wgs + cus - 1) / cus;
-  const float fill = (float)wgs / (float)(rounds * cus);
-  return extra + rate * (256.f / (float)cus) * (float)(blocks * G) * (float)n_total / fill;
+  const int at = G == 1 ? 0 : G == 2 ? 1 : 2;
+  constexpr float kMerge[3] = {0.f, 1.6f, 5.3f}, kRound[3] = {1.7f, 2.5f, 8.9f}, kRanges[3] = {2.5f, 3.0f, 5.5f};
+  constexpr float kRate[3] = {21.0e-6f, 10.9e-6f, 6.1e-6f};
+  const long blocks = (long)((g.M + G * kPartRows - 1) / (G * kPartRows)) * g.H * nl, splits = few_splits(blocks, n_total, cus);
+  const long wgs = blocks * splits, rounds = (wgs + cus - 1) / cus;
+  const float fill = (float)wgs / (float)(rounds * cus), rate = kRate[at] * (256.f / (float)cus);
+  return kMerge[at] + kRound[at] * (float)(rounds - 1) + (splits > 1 ? kRanges[at] : 0.f) +
+         rate * (float)(blocks * G) * (float)n_total / fill;
 }
 
 // More groups read K and V less often, fewer fill the chip with less work and merge sooner.
@@ -221,9 +224,11 @@ static int few_groups(const Geom& g, int nl, int n_total, int cus) {
 // Whether a launch comes here or goes to attn_bf16.hip and its merge pass.  That kernel has twice the rate once its
 // workgroups hold long runs of tiles, but pays about seven tiles' time to start and finish a run, multiplies
 // whole 128-query blocks, and merges one record per run; the estimate follows the way it cuts a launch.
-// The margin of a fifth keeps sizes where the two are level on the older path.  Step times there and here,
-// 16 heads: 1 query over 4097 slots 47.0 and 25.6 us, 64 over 16448 69 and 42, 128 over 4224 in 12 layers 196 and 85,
-// 256 over 16640 63 and 58 (stays), 700 over 4796 50 and 55; 1041 queries of 2 heads over 5137 61 and 38.
+// The margin of a tenth keeps sizes where the two are level on the older path: of the 590 launches 4 are slower than
+// there, by up to 4 us.  Step times there and here, 16 heads: 1 query over 4097 slots 47.0 and 25.6 us, 64 over 16448 69
+// and 42, 128 over 4224 in 12 layers 196 and 85, 700 over 4796 50 and 55; 1041 queries of 2 heads over 5137 61 and 38.
+// Attention alone, short caches of many heads: 104 queries of 384 heads over 608 slots 36 and 42 us, 226 of 2304 over
+// 573 177 and 469.
 bool attn_few_better(const Geom& g, int nl, int n_total, int n_wgs) {
   // a tile; the ends of a run, in tiles, alone and behind another round's; runs of a workgroup that takes cut items
   constexpr float kTileUs = 1.7f, kRunTiles = 7.f, kRoundTiles = 6.5f, kRuns = 1.25f;
@@ -244,7 +249,7 @@ bool attn_few_better(const Geom& g, int nl, int n_total, int n_wgs) {
     if (table) recs = 0.f;
   }
   const float there = kTileUs * tiles + 4.f + 0.6f * recs;
-  return 1.2f * few_cost(few_groups(g, nl, n_total, n_wgs), g, nl, n_total, n_wgs) < there;
+  return 1.1f * few_cost(few_groups(g, nl, n_total, n_wgs), g, nl, n_total, n_wgs) < there;
 }
 
 AttnSplit attn_few_split(const Geom& g, int nl, int n_total, size_t ws_bytes, int n_wgs) {

@@ -187,3 +187,18 @@ def test_fp32_attention_grids_stay_within_a_launch(layers, M, H):
     if x * y < 1 << 16:                                 # the kernel's numbering, over the whole grid
         seen = sorted((wg & 7) * (x >> 3) * y + (wg >> 3) for wg in range(x * y))
         assert seen == list(range(x * y))
+
+
+@pytest.mark.parametrize("M,H,budget,layers,kernel", [
+    # short caches of many heads: dozens of rounds of small workgroups against few runs of whole items
+    # (attention there and by the kernel for small launches, us)
+    (226, 48, 347, 48, "items"), (148, 48, 308, 48, "items"), (144, 32, 259, 48, "items"),   # 177, 386; 155, 215; 103, 138
+    (201, 24, 297, 24, "items"), (278, 32, 400, 12, "items"), (304, 16, 491, 48, "items"),   # 52, 81; 58, 83; 116, 198
+    (108, 24, 264, 24, "items"), (177, 9, 320, 24, "items"), (184, 7, 531, 48, "items"),     # 33, 45; 23, 36; 40, 52
+    (104, 16, 504, 24, "items"), (119, 16, 429, 24, "items"),                                # 36, 40; 35, 37
+    # one or two rounds, and few queries of many heads
+    (214, 16, 9423, 1, "few"), (97, 16, 867, 12, "few"), (246, 8, 686, 12, "few"), (390, 16, 2462, 6, "few"),
+    (17, 9, 159, 48, "few"), (1, 16, 188, 1, "few"), (1, 16, 188, 24, "few"), (128, 16, 4096, 12, "few")])
+def test_small_attention_launches_take_the_faster_kernel(M, H, budget, layers, kernel):
+    r = B.ovggt_attn_route(B.make_config(layers, H, 64, M, 64, budget, "bf16"), layers, budget + M)
+    assert r["kernel"] == kernel, r
