@@ -9,7 +9,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("M,n_old,H,layers", [
-    (1, 1, 1, 1), (1, 14, 3, 1), (1, 16, 1, 2),        # one tile, its last slot absent, one slot of the next
+    (1, 1, 1, 1), (1, 14, 3, 1), (8, 8, 5, 3), (1, 15, 2, 2), (1, 16, 1, 2),   # one tile, ragged and full; one slot of the next
     (15, 113, 2, 1), (16, 112, 2, 1), (17, 112, 2, 2),  # eight tiles: one a wave; one query of the next block
     (2, 254, 1, 1), (3, 254, 1, 1), (33, 1000, 1, 1),   # from where the slots are split into ranges
     (16, 4080, 1, 1), (40, 4057, 3, 2),                 # the most ranges; ranges of unequal length
