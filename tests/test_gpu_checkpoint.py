@@ -17,9 +17,10 @@ def through_half(bits):
     return np.where(np.isnan(f), np.uint16(0x7FC0), r)
 
 
-@pytest.mark.parametrize("n,H,hybrid", [(1024, 1, None), (341, 3, None), (64, 16, 0.5), (3400, 64, None)])
+@pytest.mark.parametrize("n,H,hybrid", [(1024, 1, None), (341, 3, None), (64, 16, 0.5), (3400, 64, None),
+                                        (1, 1, None), (1, 5, 0.5), (64, 1, None), (65, 1, None)])   # around 16 KB: one copy, and two
 def test_round_trip_is_bf16_through_half(n, H, hybrid):
-    cache = B.Cache(2, H, 64, 7, 64, n, "bf16", hybrid_beta=hybrid)
+    cache = B.Cache(2, H, 64, 7, 64, max(n, 7), "bf16", hybrid_beta=hybrid)
     rng = np.random.default_rng(n)
     # every pattern once where the layer is large enough, finite ones only where a centroid is built
     k = np.resize(rng.permutation(65536).astype(np.uint16), (n, H, 64))
