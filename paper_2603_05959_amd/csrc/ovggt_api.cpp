@@ -94,11 +94,14 @@ void make_geom(const ovggt_config& c, Geom* g) {
 
 int query_blocks(const ovggt_config& c) { return (c.tokens_per_frame + kQueryTile - 1) / kQueryTile; }
 
-// the larger of what a single-layer launch and an all-layers launch need
+// K and V of one token: what a checkpoint stages at the least
+size_t checkpoint_row_bytes(const ovggt_config& c) { return (size_t)2 * c.n_heads * c.head_dim * 2; }
+
+// the largest of what a single-layer launch, an all-layers launch and a checkpoint need
 size_t ws_bytes_for(const ovggt_config& c) {
   if (c.dtype != OVGGT_BF16) return up256(attn_f32_ws_bytes(c.n_layers * c.n_heads, c.tokens_per_frame));
   const size_t one = attn_ws_bytes(c.n_heads, query_blocks(c)), all = attn_ws_bytes(c.n_layers * c.n_heads, query_blocks(c));
-  return up256(one > all ? one : all);
+  return up256(std::max({one, all, checkpoint_row_bytes(c)}));
 }
 
 // attention workgroups of a device of `cus` compute units
@@ -172,10 +175,9 @@ int flush_pending(ovggt_cache* c, int l0, int nl, hipStream_t s) {
 }
 
 // Rows of a bf16 layer that fit the handle's workspace at a time when it serves as the staging area of
-// a checkpoint: free whenever no attention launch is in flight.  At least one (a record of the
-// attention is larger than the largest row).
+// a checkpoint: free whenever no attention launch is in flight.  At least one: ws_bytes_for sees to it.
 int checkpoint_rows(const ovggt_cache* c, int n) {
-  const size_t fit = ws_bytes_for(c->cfg) / ((size_t)2 * c->g.H * c->g.d * c->g.esize);
+  const size_t fit = ws_bytes_for(c->cfg) / checkpoint_row_bytes(c->cfg);
   return fit < (size_t)n ? (int)fit : n;
 }
 

@@ -202,3 +202,11 @@ def test_fp32_attention_grids_stay_within_a_launch(layers, M, H):
 def test_small_attention_launches_take_the_faster_kernel(M, H, budget, layers, kernel):
     r = B.ovggt_attn_route(B.make_config(layers, H, 64, M, 64, budget, "bf16"), layers, budget + M)
     assert r["kernel"] == kernel, r
+
+
+def test_workspace_holds_a_staged_row_of_any_width():
+    """Checkpoints of bf16 layers pass through the workspace in whole rows of K and V."""
+    for heads in (1, 16, 64, 1023, 1024):
+        for layers, M in ((1, 1), (2, 1), (1, 1374)):
+            ws = B.ovggt_cache_query_bytes(B.make_config(layers, heads, 64, M, 64, 2 * M, "bf16"))[2]
+            assert ws >= 2 * heads * 64 * 2
