@@ -283,19 +283,21 @@ static int global_attn_impl(ovggt_cache* c, int layer, const void* q, const void
         for (hipEvent_t x : ev)
           if (x) c->prof_free.push_back(x);
     }
-    if (attn_few_better(g, nl, n + g.M, c->n_wgs)) {                        // one kernel, merges included
+    const bool few = attn_few_better(g, nl, n + g.M, c->n_wgs);
+    if (few) {                                                    // one kernel, merges included
       e = have ? hipEventRecord(ev[0], s) : hipSuccess;
       if (e == hipSuccess)
         e = launch_attn_few(g, c->kv, c->meta, l0, nl, q, out, n + g.M, c->scale, ws, ws_bytes, c->n_wgs,
                             c->cfg.out_dtype == OVGGT_F32, s);
-      for (int i = 1; i < 3 && have && e == hipSuccess; ++i) e = hipEventRecord(ev[i], s);
+      if (have && e == hipSuccess) e = hipEventRecord(ev[1], s);
     } else {
       e = launch_attn_bf16(g, c->kv, l0, nl, q, out, n + g.M, c->scale, ws, ws_bytes, c->n_wgs,
                            c->cfg.out_dtype == OVGGT_F32, s, have ? ev : nullptr);
     }
     if (have) {
       c->prof_pending[OVGGT_PROF_ATTN].push_back({ev[0], ev[1]});
-      c->prof_pending[OVGGT_PROF_COMBINE].push_back({ev[1], ev[2]});   // shares ev[1] as its start
+      if (few) c->prof_free.push_back(ev[2]);                          // no merge pass: nothing of that class to count
+      else c->prof_pending[OVGGT_PROF_COMBINE].push_back({ev[1], ev[2]});   // shares ev[1] as its start
     }
   } else {
     ProfScope ps(c, OVGGT_PROF_ATTN, s, prof_attn);

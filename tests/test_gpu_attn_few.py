@@ -69,3 +69,26 @@ def test_rows_behind_the_last_slot_carry_no_weight():
     cache.step(q, k, v, torch.ones(1, M, 64).bfloat16().cuda(), None, o)
     assert torch.isfinite(o).all()
     cache.close()
+
+
+@pytest.mark.parametrize("dtype,M,H,budget,kernel", [("bf16", 1, 4, 40, "few"), ("bf16", 700, 16, 4096, "items"), ("f32", 40, 2, 100, "f32")])
+def test_timing_counts_the_launches_there_are(dtype, M, H, budget, kernel):
+    """Bracketed launches per kernel class: a merge pass only where there is one."""
+    import torch
+    cache = B.Cache(1, H, 64, M, 64, budget, dtype)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    x, r = torch.randn(1, M, H, 64, device="cuda").to(dt), torch.ones(1, M, 64, device="cuda").to(dt)
+    out = cache.new_output()
+    for level in (1, 2):
+        while cache.size(0) < budget:                   # the last frames are on a full cache
+            cache.step(x, x, x, r, None, out)
+        B.ovggt_profile_read(cache.h, cache.stream)
+        B.ovggt_profile_enable(cache.h, level, 1)
+        for _ in range(5):
+            cache.step(x, x, x, r, None, out)
+        assert B.ovggt_attn_route(cache.cfg, 1, budget + M)["kernel"] == kernel
+        got = B.ovggt_profile_read(cache.h, cache.stream)
+        assert got["attn"][1] == 5 and got["combine"][1] == (5 if kernel == "items" else 0)
+        assert got["append"][1] == got["score_select"][1] == (5 if level == 2 else 0)
+        assert got["attn"][0] > 0
+    cache.close()
