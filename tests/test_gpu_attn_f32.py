@@ -11,7 +11,8 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("M,n_old,H,layers", [
     (1, 1, 1, 1), (1, 14, 3, 1), (8, 8, 5, 3), (1, 15, 2, 2), (1, 16, 1, 2),   # one tile, ragged and full; one slot of the next
     (15, 113, 2, 1), (16, 112, 2, 1), (17, 112, 2, 2),  # eight tiles: one a wave; one query of the next block
-    (2, 254, 1, 1), (3, 254, 1, 1), (33, 1000, 1, 1),   # from where the slots are split into ranges
+    (2, 254, 1, 1), (3, 254, 1, 1),                     # sixteen tiles, two for each wave; one more
+    (1, 495, 1, 1), (1, 496, 1, 1), (33, 1000, 1, 1),   # the last size in one range, the first in two; four ranges
     (16, 4080, 1, 1), (40, 4057, 3, 2),                 # the most ranges; ranges of unequal length
     (272, 1300, 16, 1), (97, 2048, 4, 24),              # more blocks than CUs: two or more ranges each, and one
 ])
@@ -44,25 +45,25 @@ def test_matches_fp64_softmax(M, n_old, H, layers):
     cache.close()
 
 
-def test_rows_behind_the_last_slot_are_not_read():
+@pytest.mark.parametrize("n_old", [3, 10, 17])           # one tile for one wave; the second tile of two, ragged and nearly full
+def test_rows_behind_the_last_slot_are_not_read(n_old):
     """Evicted entries stay in memory behind the resident ones, infinities and NaN among them."""
     import torch
-    M, H, Bq = 5, 2, 19
+    M, H, Bq = 5, 2, 40
     gen = torch.Generator().manual_seed(2)
     cache = B.Cache(1, H, 64, M, 64, Bq, "f32")
-    out = cache.new_output()
-    for t in range(4):                                  # the frame that overflows the budget is all infinite, and is evicted
+    ids, ones, zeros = np.arange(Bq, dtype=np.uint32), np.ones(Bq, np.float32), np.zeros(Bq, np.uint8)
+    for l, poison in enumerate((float("inf"), float("nan"))):
+        fill = np.full((Bq, H, 64), poison, np.float32)
+        cache.import_(0, 8, ids, fill, fill, ones, zeros)            # every slot, before the few that stay resident
+        ko, vo = (torch.randn(n_old, H, 64, generator=gen) for _ in range(2))
+        cache.import_(0, 8, ids[:n_old], ko.numpy(), vo.numpy(), ones[:n_old], zeros[:n_old])
         q, k, v = (torch.randn(1, M, H, 64, generator=gen) for _ in range(3))
-        r = torch.ones(1, M, 64)
-        if t == 3:
-            k[:] = float("inf"); v[:] = float("nan"); r[:] = 0.01
-        cache.step(q.cuda(), k.cuda(), v.cuda(), r.cuda(), None, out)
-    e = cache.export(0)
-    keep = np.isfinite(e["k"]).all(axis=(1, 2))
-    cache.import_(0, 4, e["ids"][keep], e["k"][keep], e["v"][keep], e["ss"][keep], e["flags"][keep])
-    q, k, v = (torch.randn(1, 1, H, 64, generator=gen).repeat(1, M, 1, 1) for _ in range(3))
-    cache.step(q.cuda(), k.cuda(), v.cuda(), torch.ones(1, M, 64).cuda(), None, out)
-    assert torch.isfinite(out).all()
+        out = cache.new_output()
+        cache.step(q.cuda(), k.cuda(), v.cuda(), torch.ones(1, M, 64).cuda(), None, out)
+        kk, vv = torch.cat([ko, k[0]]).double(), torch.cat([vo, v[0]]).double()
+        ref = torch.einsum("hmn,nhd->mhd", torch.softmax(torch.einsum("mhd,nhd->hmn", q[0].double(), kk) / 8.0, dim=-1), vv)
+        assert (out[0].cpu().double() - ref).norm() / ref.norm() < 5e-6, poison
     cache.close()
 
 

@@ -12,16 +12,19 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("M,n_old,H,layers,out", [
     (1, 1, 1, 1, "f32"), (1, 30, 3, 1, "bf16"), (1, 31, 1, 2, "f32"), (1, 32, 1, 1, "f32"),   # one tile, ragged and full; two
     (15, 241, 2, 1, "f32"), (16, 240, 2, 1, "bf16"), (17, 240, 2, 2, "f32"),   # eight tiles: one a wave; one query of the next block
+    (1, 255, 1, 1, "f32"), (1, 256, 1, 1, "f32"),                   # the last size in one range, the first in two
     (1, 4095, 1, 1, "f32"), (5, 4200, 3, 1, "bf16"),                # the most ranges; ranges of unequal length
     (33, 16000, 16, 1, "f32"), (64, 8000, 16, 1, "bf16"),           # two groups, the last one of padding; two full ones
     (128, 16384, 16, 1, "f32"), (97, 4096, 16, 12, "bf16"),         # four groups, split and not
     (1041, 4096, 1, 1, "f32"), (513, 2048, 4, 1, "f32"),            # many blocks of few heads
-    (700, 4096, 16, 1, "f32"), (400, 4096, 16, 1, "f32"),           # the large kernel, and near the line
+    (300, 4096, 16, 1, "f32"), (400, 4096, 16, 1, "f32"), (700, 4096, 16, 1, "f32"),   # here, and the large kernel
 ])
 def test_matches_fp64_softmax(M, n_old, H, layers, out):
     import torch
     gen = torch.Generator().manual_seed(M * 1000 + n_old)
     cache = B.Cache(layers, H, 64, M, 64, max(n_old, M), "bf16", out_dtype=out)
+    kernel = B.ovggt_attn_route(cache.cfg, layers, n_old + M)["kernel"]
+    assert kernel == ("items" if M in (400, 700) else "few")
     rnd = lambda *s: torch.randn(s, generator=gen, dtype=torch.float32).bfloat16()
     old = [(rnd(n_old, H, 64), rnd(n_old, H, 64)) for _ in range(layers)]
     for l, (k, v) in enumerate(old):
@@ -42,32 +45,32 @@ def test_matches_fp64_softmax(M, n_old, H, layers, out):
                 err = ((got[l, :, h] - ref).norm() / ref.norm()).item()
                 # weights rounded to 11 bits (relative errors of 2^-11 / sqrt(3) at most in the mean, as random signs add up);
                 # the kernel for large launches rounds the scaled queries to 11 bits too; a bf16 output has 8 bits
-                assert err < 2.0 ** -11 + (2.0 ** -11 if M in (400, 700) else 0.0) + (2.0 ** -9 if out == "bf16" else 0.0), (rep, l, h, err)
+                assert err < 2.0 ** -11 + (2.0 ** -11 if kernel == "items" else 0.0) + (2.0 ** -9 if out == "bf16" else 0.0), (rep, l, h, err)
         e = [cache.export(l) for l in range(layers)]
         old = [tuple(torch.from_numpy(x[n]).bfloat16() for n in "kv") for x in e]
     cache.close()
 
 
-def test_rows_behind_the_last_slot_carry_no_weight():
+@pytest.mark.parametrize("n_old", [3, 17, 40])           # one tile; its last rows; the second tile of two
+def test_rows_behind_the_last_slot_carry_no_weight(n_old):
     """Evicted entries stay in memory behind the resident ones, NaN among them."""
     import torch
-    M, H, Bq = 5, 2, 19
+    M, H, Bq = 5, 2, 70
     gen = torch.Generator().manual_seed(2)
     cache = B.Cache(1, H, 64, M, 64, Bq, "bf16")
+    assert B.ovggt_attn_route(cache.cfg, 1, n_old + M)["kernel"] == "few"
+    ids, ones, zeros = np.arange(Bq, dtype=np.uint32), np.ones(Bq, np.float32), np.zeros(Bq, np.uint8)
+    fill = np.full((Bq, H, 64), 0x7FC0, np.uint16)                   # NaN in every slot, before the few that stay resident
+    cache.import_(0, 14, ids, fill, fill, ones, zeros)
+    ko, vo = (torch.randn(n_old, H, 64, generator=gen).bfloat16() for _ in range(2))
+    bits = lambda x: x.view(torch.int16).numpy().view(np.uint16)
+    cache.import_(0, 14, ids[:n_old], bits(ko), bits(vo), ones[:n_old], zeros[:n_old])
+    q, k, v = (torch.randn(1, M, H, 64, generator=gen).bfloat16() for _ in range(3))
     o = cache.new_output()
-    for t in range(4):                                  # the frame that overflows the budget is all NaN, and is evicted
-        q, k, v = (torch.randn(1, M, H, 64, generator=gen) for _ in range(3))
-        r = torch.ones(1, M, 64)
-        if t == 3:
-            k[:] = float("nan"); v[:] = float("nan"); r[:] = 0.01
-        cache.step(*(x.bfloat16().cuda() for x in (q, k, v, r)), None, o)
-    e = cache.export(0)
-    keep = np.isfinite(e["k"]).all(axis=(1, 2))
-    bits = [torch.from_numpy(e[n][keep]).bfloat16().view(torch.int16).numpy().view(np.uint16) for n in "kv"]
-    cache.import_(0, 4, e["ids"][keep], *bits, e["ss"][keep], e["flags"][keep])
-    q, k, v = (torch.randn(1, 1, H, 64, generator=gen).repeat(1, M, 1, 1).bfloat16().cuda() for _ in range(3))
-    cache.step(q, k, v, torch.ones(1, M, 64).bfloat16().cuda(), None, o)
-    assert torch.isfinite(o).all()
+    cache.step(q.cuda(), k.cuda(), v.cuda(), torch.ones(1, M, 64).bfloat16().cuda(), None, o)
+    kk, vv = torch.cat([ko, k[0]]).half().double(), torch.cat([vo, v[0]]).half().double()
+    ref = torch.einsum("hmn,nhd->mhd", torch.softmax(torch.einsum("mhd,nhd->hmn", q[0].double(), kk) / 8.0, dim=-1), vv)
+    assert (o[0].cpu().double() - ref).norm() / ref.norm() < 2.0 ** -11          # as above
     cache.close()
 
 
