@@ -52,11 +52,21 @@ def compare_cache(cache, orc, layer=0, kv=True):
         assert np.array_equal(e["v"], stored_v(orc.v, cache.dtype))
 
 
+def assert_kernel(cache, frame, kernel, layers=1):
+    """The attention kernel that a shape is here for ("items": 128-query items and a merge pass, "few": the one
+    for small launches) is the one that this frame takes, so that no change of the dispatch empties a test."""
+    n_total = min(frame * cache.M, cache.B) + cache.M
+    assert B.ovggt_attn_route(cache.cfg, layers, n_total)["kernel"] == kernel, (cache.M, cache.H, n_total, layers)
+
+
 def run_stream(cfg, layer=0, attn_frames=None, cache_every=1, resid_fn=None, q_rows=None, log=None, smooth=None,
-               hybrid_beta=None, qkv_fn=None):
-    """Drive both sides over cfg.T frames of one layer; returns max attention error."""
+               hybrid_beta=None, qkv_fn=None, kernel=None, tol=None):
+    """Drive both sides over cfg.T frames of one layer; returns max attention error.  `kernel`: the attention
+    kernel that the last frame has to take."""
     torch = _torch()
     cache = make_cache(cfg, L=1, smooth=smooth, hybrid_beta=hybrid_beta)
+    if kernel is not None:
+        assert_kernel(cache, cfg.T - 1, kernel)
     orc = oc.OracleCache(cfg.M, cfg.H, cfg.d, cfg.B, smooth=smooth, hybrid_beta=hybrid_beta)
     out = cache.new_output()[0]
     worst = 0.0
@@ -80,7 +90,7 @@ def run_stream(cfg, layer=0, attn_frames=None, cache_every=1, resid_fn=None, q_r
                 o_gpu = o_gpu[q_rows]
             err = rel_err(o_gpu, o_ref)
             worst = max(worst, err)
-            assert err < TOL[cfg.dtype], f"frame {t}: attention error {err:.3e}"
+            assert err < (tol or TOL[cfg.dtype]), f"frame {t}: attention error {err:.3e}"
         orc.update(f["r"], f["a"])
         assert cache.size(0) == orc.n == min((t + 1) * cfg.M, cfg.B)
         if t % cache_every == 0 or t == cfg.T - 1:
@@ -97,11 +107,13 @@ def test_cfg0_tiny_f32_full_stream():
     print("cfg0 worst attention err/RMS:", worst)
 
 
-def test_bf16_ragged_small():
-    # 200 queries (1.6 query blocks), 900 slots at steady state (7 tiles + tail of 4), odd head count,
-    # residual width that is not a power of two
-    cfg = synth.preset(1, M=200, H=3, C=200, B=700, T=9, n_special=3)
-    worst = run_stream(cfg)
+@pytest.mark.parametrize("M,H,B_,T,kernel", [
+    (200, 3, 700, 9, "few"),             # 200 queries (1.6 query blocks), 900 slots at steady state (7 tiles + tail of 4), odd head count,
+    (1041, 7, 4160, 7, "items"),         # 8.1 query blocks, 5201 slots (40 tiles + tail of 81), odd head count,
+])                                       # residual width that is not a power of two
+def test_bf16_ragged_small(M, H, B_, T, kernel):
+    cfg = synth.preset(1, M=M, H=H, C=200, B=B_, T=T, n_special=3)
+    worst = run_stream(cfg, kernel=kernel, q_rows=None if M < 1000 else np.r_[0:40, 500:540, 1000:1041])
     print("ragged worst attention err/RMS:", worst)
 
 
@@ -135,25 +147,35 @@ def _hard_values(kind):
     return fn
 
 
+# 6 frames of 200 tokens under a budget that keeps everything: 1200 slots = 9 tiles + a tail, every frame's
+# output compared; and 5 frames of 1041 tokens, 5205 slots = 40 tiles + a tail, by the kernel of 128-query items:
+# the tiles of a head are shared by both wave sets, or, for the odd ninth block, of two heads in one item
+@pytest.mark.parametrize("M,H,B_,T,kernel", [(200, 2, 2000, 6, "few"), (1041, 16, 6000, 5, "items")])
 @pytest.mark.parametrize("kind", ["peaky", "rising", "falling", "constant", "zero_q", "big_v", "tiny_v", "outlier_key",
                                   "all_low"])
-def test_attention_hard_value_distributions(kind):
-    # 6 frames of 200 tokens under a budget that keeps everything: 1200 slots = 9 tiles + a tail,
-    # every frame's output compared
-    cfg = synth.preset(1, M=200, H=2, C=64, B=2000, T=6, n_special=2)
-    worst = run_stream(cfg, qkv_fn=_hard_values(kind))
+def test_attention_hard_value_distributions(kind, M, H, B_, T, kernel):
+    cfg = synth.preset(1, M=M, H=H, C=64, B=B_, T=T, n_special=2)
+    # The queries rounded to half after scaling are off by 2.0e-4 rms, logits of a spread of 16 so by 3.2e-3 and the
+    # ratio of two weights by 4.5e-3; an output between two values moves by up to a quarter of that times their
+    # difference, both normal: the largest product of two normals among N outputs is about ln N = 13 for 281 rows of
+    # 16 heads (1/4 * 4.5e-3 * sqrt(2) * 13 = 2.1e-2 of values near 1) and half as far out again once in a while.
+    tol = 3e-2 if kind == "peaky" and kernel == "items" else None
+    worst = run_stream(cfg, qkv_fn=_hard_values(kind), kernel=kernel, tol=tol, q_rows=None if M < 600 else np.r_[0:100, 480:600, 980:1041])
     print(f"{kind}: worst attention err/RMS {worst:.3e}")
 
 
-# (2100, 2500) has 17 query blocks: more than the merge pass's table of records holds, so the pass
-# lists each item's records itself; the last two have an even number of heads and three or five
-# query blocks, so workgroups pass from items whose two halves share one head's tiles to the mixed
-# item of the odd last block and back, several pieces each
-@pytest.mark.parametrize("M,B,H,C", [(1, 64, 1, 64), (37, 74, 2, 1024), (130, 1000, 5, 4096), (128, 256, 16, 8),
-                                     (2100, 2500, 2, 64), (300, 6000, 4, 64), (520, 3000, 2, 128)])
-def test_bf16_odd_shapes(M, B, H, C):
-    cfg = synth.preset(1, M=M, H=H, C=C, B=B, T=max(6, 2 * B // M + 3) if M > 1 else 70, n_special=min(M - 1, 2))
-    run_stream(cfg)
+# Small launches first.  (2100, 16) has 17 query blocks: more than the merge pass's table of records holds, so the
+# pass lists each item's records itself.  (800, 16) has seven query blocks and an even number of heads: workgroups
+# pass from items whose two halves share one head's tiles to the mixed item of the odd last block and back, several
+# pieces each; (1374, 9) has an odd number of heads and a half item at the end.
+@pytest.mark.parametrize("M,B,H,C,kernel", [
+    (1, 64, 1, 64, "few"), (37, 74, 2, 1024, "few"), (130, 1000, 5, 4096, "few"), (128, 256, 16, 8, "few"),
+    (2100, 2500, 2, 64, "few"), (300, 6000, 4, 64, "few"), (520, 3000, 2, 128, "few"),
+    (2100, 4300, 16, 64, "items"), (800, 4000, 16, 128, "items"), (1374, 4200, 9, 64, "items")])
+def test_bf16_odd_shapes(M, B, H, C, kernel):
+    T = 70 if M == 1 else max(6, 2 * B // M + 3) if kernel == "few" else B // M + 3
+    cfg = synth.preset(1, M=M, H=H, C=C, B=B, T=T, n_special=min(M - 1, 2))
+    run_stream(cfg, kernel=kernel, q_rows=None if kernel == "few" else np.r_[0:60, 620:680, M - 60:M])
 
 
 def test_f32_shapes_with_eviction_and_ties():
@@ -285,14 +307,17 @@ def test_cfg2_24_layers_kept_ids_deep_into_eviction():
     cache.close()
 
 
-def test_values_beyond_the_half_range_saturate_and_set_status():
+@pytest.mark.parametrize("M,H,B_,kernel", [(130, 2, 600, "few"), (1041, 16, 4096, "items")])
+def test_values_beyond_the_half_range_saturate_and_set_status(M, H, B_, kernel):
     """bf16 handles cache K and V as IEEE half: elements beyond +-65504 (bf16 reaches 3e38) are
     saturated, the status word reports it, export returns the saturated image, and attention
     runs on that image."""
     torch = _torch()
-    cfg = synth.preset(1, M=130, H=2, C=64, B=600, T=3, n_special=2)
+    cfg = synth.preset(1, M=M, H=H, C=64, B=B_, T=3, n_special=2)
     cache = make_cache(cfg, L=1)
+    assert_kernel(cache, 1, kernel)
     out = cache.new_output()[0]
+    rows = slice(0, 130)
     ks, vs = [], []
     for t in range(cfg.T):
         f = synth.frame_inputs(cfg, 0, t)
@@ -306,22 +331,32 @@ def test_values_beyond_the_half_range_saturate_and_set_status():
         st = cache.status(0)                       # reads and clears
         assert st == (B.OVGGT_STATUS_VRANGE if t == 1 else 0), (t, st)
         kc, vc = oc.cached_half(np.concatenate(ks)), oc.cached_half(np.concatenate(vs))
-        ref = oc.attention(f["q"], kc, vc)
-        assert rel_err(out.float().cpu().numpy().astype(np.float64), ref) < TOL["bf16"], t
+        ref = oc.attention(f["q"][rows], kc, vc)
+        o = out.float().cpu().numpy().astype(np.float64)[rows]
+        if kernel == "items":
+            # a column of V that holds 65504 in one slot is as large as that slot's weights, in two of the sixteen heads
+            # only: thousands beside an RMS of tens.  Errors of a weight are relative to it, so is the bound there.
+            size = np.maximum(np.abs(ref), np.sqrt((ref ** 2).mean()))
+            assert (np.abs(o - ref) / size).max() < TOL["bf16"], t
+        else:
+            assert rel_err(o, ref) < TOL["bf16"], t
     e = cache.export(0)
     kc, vc = oc.cached_half(np.concatenate(ks)), oc.cached_half(np.concatenate(vs))
-    assert np.abs(kc).max() == 65504.0 and np.abs(vc).max() == 65504.0 and vc[130 + 8, 0, 0] == 65280.0
+    assert np.abs(kc).max() == 65504.0 and np.abs(vc).max() == 65504.0 and vc[M + 8, 0, 0] == 65280.0
     assert np.array_equal(e["k"], synth.quantise(kc, "bf16"))
     assert np.array_equal(e["v"], synth.quantise(vc, "bf16"))
     cache.close()
 
 
-def test_scaled_query_beyond_the_half_range_is_clamped():
+@pytest.mark.parametrize("M,H,B_,kernel", [(130, 2, 600, "few"), (1041, 16, 4096, "items")])
+def test_scaled_query_beyond_the_half_range_is_clamped(M, H, B_, kernel):
     """A query element whose product with scale*log2(e) leaves the half range is clamped to
     +-65504, so the output stays finite and equals attention with the clamped query."""
     torch = _torch()
-    cfg = synth.preset(1, M=130, H=2, C=64, B=600, T=2, n_special=2)
+    cfg = synth.preset(1, M=M, H=H, C=64, B=B_, T=2, n_special=2)
     cache = make_cache(cfg, L=1)
+    assert_kernel(cache, 1, kernel)
+    rows = slice(0, 130)
     out = cache.new_output()[0]
     c = (1.0 / 8.0) * 1.4426950408889634
     ks, vs = [], []
@@ -335,9 +370,9 @@ def test_scaled_query_beyond_the_half_range_is_clamped():
         ks.append(f["k"]); vs.append(f["v"])
         o = out.float().cpu().numpy().astype(np.float64)
         assert np.isfinite(o).all()
-        q_eff = np.clip(f["q"].astype(np.float64), -65504.0 / c, 65504.0 / c)
+        q_eff = np.clip(f["q"].astype(np.float64)[rows], -65504.0 / c, 65504.0 / c)
         ref = oc.attention(q_eff, np.concatenate(ks), np.concatenate(vs))
-        assert rel_err(o, ref) < TOL["bf16"], t
+        assert rel_err(o[rows], ref) < TOL["bf16"], t
     assert cache.status(0) == 0
     cache.close()
 
@@ -460,16 +495,21 @@ def test_worst_case_compaction_rising_scores():
 
 
 @pytest.mark.parametrize("shape", [
-    dict(M=150, H=2, C=256, B=400, T=7, L=3),          # 3 head pairs: one chunk per workgroup
-    dict(M=300, H=8, C=64, B=5000, T=5, L=4),          # 16 head pairs: two rounds per XCD, tile segments
-    dict(M=130, H=16, C=64, B=300, T=4, L=3),          # 24 head pairs: three rounds, short caches
-    dict(M=600, H=16, C=64, B=1000, T=4, L=8),         # 64 head pairs x 5 query blocks: whole items per workgroup for a
-                                                       # round, the 8 left over per XCD cut into 4-tile chunks (5 pieces each)
+    (dict(M=150, H=2, C=256, B=400, T=7, L=3), "few"),
+    (dict(M=300, H=8, C=64, B=5000, T=5, L=4), "few"),
+    (dict(M=130, H=16, C=64, B=300, T=4, L=3), "few"),
+    (dict(M=1374, H=2, C=64, B=6800, T=6, L=3), "items"),   # 3 head pairs: chunks of one head pair, tile segments
+    (dict(M=700, H=8, C=64, B=2800, T=6, L=4), "items"),    # 16 head pairs: two rounds per XCD, tile segments
+    (dict(M=1041, H=16, C=64, B=1100, T=3, L=3), "items"),  # 24 head pairs: three rounds, short caches
+    (dict(M=600, H=16, C=64, B=1000, T=4, L=8), "items"),   # 64 head pairs x 5 query blocks: whole items per workgroup for a
+                                                            # round, the 8 left over per XCD cut into 4-tile chunks (5 pieces each)
 ])
 def test_batched_layers_match_per_layer_oracle(shape):
+    shape, kernel = shape
     cfg = synth.preset(2, n_special=5, **shape)
     torch = _torch()
     cache = make_cache(cfg)
+    assert_kernel(cache, cfg.T - 1, kernel, layers=cfg.L)
     orcs = [oc.OracleCache(cfg.M, cfg.H, cfg.d, cfg.B) for _ in range(cfg.L)]
     out = cache.new_output()
     for t in range(cfg.T):
@@ -1014,11 +1054,13 @@ def test_set_protect_argument_and_state_errors():
     cache.close()
 
 
-def test_bf16_output_is_the_rounded_fp32_output():
+@pytest.mark.parametrize("M,H,B_,kernel", [(200, 3, 500, "few"), (1374, 9, 4100, "items"), (800, 16, 3200, "items")])
+def test_bf16_output_is_the_rounded_fp32_output(M, H, B_, kernel):
     """out_dtype = bf16 stores RNE(bf16) of exactly the value the fp32-output run stores."""
-    cfg = synth.preset(1, M=200, H=3, C=64, B=500, T=5, n_special=3)
+    cfg = synth.preset(1, M=M, H=H, C=64, B=B_, T=5, n_special=3)
     torch = _torch()
     c32 = make_cache(cfg, L=1)
+    assert_kernel(c32, cfg.T - 1, kernel)
     c16 = B.Cache(1, cfg.H, cfg.d, cfg.M, cfg.C, cfg.B, cfg.dtype, out_dtype="bf16")
     o32, o16 = c32.new_output()[0], c16.new_output()[0]
     assert o16.dtype == torch.bfloat16
@@ -1031,18 +1073,21 @@ def test_bf16_output_is_the_rounded_fp32_output():
     c32.close(); c16.close()
 
 
-def test_captured_step_replayed_from_a_hip_graph_matches_the_oracle():
+@pytest.mark.parametrize("M,H,B_,T,kernel", [(300, 4, 1500, 32, "few"), (800, 16, 3200, 31, "items")])
+def test_captured_step_replayed_from_a_hip_graph_matches_the_oracle(M, H, B_, T, kernel):
     """One steady-state step (append with the carried moves, attention, merge, score/select) is
     captured into a HIP graph and replayed for 20 further frames, the inputs copied into the captured
     buffers before each replay: every replay's attention output against the oracle, and the cache
     (kept ids, layout, scores, flags, K, V) bit-exact at the end.  No kernel argument depends on the
     frame: the token ids come from device memory."""
     torch = _torch()
-    cfg = synth.preset(1, M=300, H=4, C=256, B=1500, T=32, n_special=5)
+    cfg = synth.preset(1, M=M, H=H, C=256, B=B_, T=T, n_special=5)
     cache = make_cache(cfg, L=1)
+    assert_kernel(cache, T, kernel)
     orc = oc.OracleCache(cfg.M, cfg.H, cfg.d, cfg.B)
     out = cache.new_output()[0]
-    eager = 9                                             # 5 frames fill the cache, 4 more evict
+    rows = slice(0, cfg.M) if M < 600 else np.r_[0:60, 740:800]
+    eager = T - 23                                        # the cache is full after 5 (4) frames, 4 more evict
     f = synth.frame_inputs(cfg, 0, 0)
     fixed = [dev(f[x], cfg) for x in "qkvr"] + [torch.from_numpy(f["a"]).cuda()]
 
@@ -1054,9 +1099,11 @@ def test_captured_step_replayed_from_a_hip_graph_matches_the_oracle():
         return f
 
     def check(t, f):
-        ref = orc.step(f["q"], f["k"], f["v"], f["r"], f["a"])
+        orc.append(f["k"], f["v"])
+        ref = oc.attention(f["q"][rows], orc.k, orc.v)
+        orc.update(f["r"], f["a"])
         torch.cuda.synchronize()
-        err = rel_err(out.float().cpu().numpy().astype(np.float64), ref)
+        err = rel_err(out.float().cpu().numpy().astype(np.float64)[rows], ref)
         assert err < TOL["bf16"], f"frame {t}: attention error {err:.3e}"
 
     for t in range(eager):

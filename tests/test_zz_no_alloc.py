@@ -10,11 +10,13 @@ from paper_2603_05959_amd import synth
 pytestmark = pytest.mark.gpu
 
 
-def _stream_both_ways(cfg, frames):
+def _stream_both_ways(cfg, frames, kernel):
     """The same frames through two handles, one per entry point; returns the last frame's inputs and
     the reference output of the oracle for it."""
     import torch
     caches = [B.Cache(1, cfg.H, cfg.d, cfg.M, cfg.C, cfg.B, cfg.dtype) for _ in range(2)]
+    n_total = min((frames - 1) * cfg.M, cfg.B) + cfg.M
+    assert B.ovggt_attn_route(caches[0].cfg, 1, n_total)["kernel"] == kernel         # the one the stream is here for
     outs = [c.new_output()[0] for c in caches]
     orc = oc.OracleCache(cfg.M, cfg.H, cfg.d, cfg.B)
     for t in range(frames):
@@ -42,10 +44,12 @@ def _stream_both_ways(cfg, frames):
 
 
 def test_static_workspace_entry_point_matches_the_regular_one_twice_in_a_row():
-    # two calls in a row share the library's array: a larger launch (11 tiles, several pieces per query
-    # block) and then a smaller one (2 tiles), each compared with ovggt_global_attn and the oracle
-    _stream_both_ways(synth.preset(1, M=300, H=4, C=128, B=1100, T=6, n_special=3), 6)
-    _stream_both_ways(synth.preset(1, M=70, H=2, C=64, B=200, T=5, n_special=1), 5)
+    # calls in a row share the library's array: larger launches (several pieces per query block) and then
+    # smaller ones, of either attention kernel, each compared with ovggt_global_attn and the oracle
+    _stream_both_ways(synth.preset(1, M=1041, H=16, C=128, B=3200, T=5, n_special=3), 5, "items")
+    _stream_both_ways(synth.preset(1, M=800, H=16, C=64, B=3200, T=6, n_special=3), 6, "items")
+    _stream_both_ways(synth.preset(1, M=300, H=4, C=128, B=1100, T=6, n_special=3), 6, "few")
+    _stream_both_ways(synth.preset(1, M=70, H=2, C=64, B=200, T=5, n_special=1), 5, "few")
 
 
 def test_static_workspace_entry_point_rejects_launches_beyond_its_array():
