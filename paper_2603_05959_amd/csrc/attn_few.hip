@@ -186,12 +186,13 @@ attn_few_kernel(Geom g, AttnFewParams p) {
                      });
 }
 
-// Ranges of the slots for each block of queries: one more for every CU that would idle, as long as a range keeps a
-// tile for each wave (ranges for two workgroups a CU: 24.7 -> 21.7 us at 1 query of 2 heads over 2049 slots, but
-// 37 -> 57 at 128 of 16 over 4224).
+// Ranges of the slots for each block of queries: one more for every CU that would idle, two from where both keep a tile
+// for each wave (attention of 1 query of 16 heads over 301 slots: 8.3 us with one, 10.3 with two; over 561 11.1 and 10.9),
+// then one for every eight tiles begun (over 801 slots 11.1, with one less 11.4).  Ranges for two workgroups a CU took 21.7
+// us instead of 24.7 at 1 query of 2 heads over 2049 slots, but 57 instead of 37 at 128 of 16 over 4224.
 static long few_splits(long blocks, int n_total, int cus) {
-  if (blocks >= cus) return 1;
-  const long most = ((n_total + 31) / 32 + kPartWaves - 1) / kPartWaves;
+  const long tiles = (n_total + 31) / 32, most = (tiles + kPartWaves - 1) / kPartWaves;
+  if (blocks >= cus || tiles < 2 * kPartWaves) return 1;
   long s = cus / blocks;
   if (s > most) s = most;
   return s > kMaxSplits ? kMaxSplits : s;
@@ -201,7 +202,7 @@ static long few_splits(long blocks, int n_total, int cus) {
 // larger merge adds, what each round of workgroups after the first adds (first loads and merge of the waves), what the
 // merge of ranges adds, and the rate at which 256 CUs take 16 queries past a slot, over the share of the CUs that the
 // rounds fill.  Fit over 590 launches of 1 to 2100 queries, 16 to 32 K slots and 1 to 2304 heads, all three G: 5 to 6 %
-// rms.  Without the part for further rounds 226 queries over 573 slots of 2304 heads, 36 rounds of 13 us, counted as one.
+// rms.  The part per round: 226 queries over 573 slots of 2304 heads are 36 rounds of 13 us with G = 4.
 static float few_cost(int G, const Geom& g, int nl, int n_total, int cus) {
   const int at = G == 1 ? 0 : G == 2 ? 1 : 2;
   constexpr float kMerge[3] = {0.f, 1.6f, 5.3f}, kRound[3] = {1.7f, 2.5f, 8.9f}, kRanges[3] = {2.5f, 3.0f, 5.5f};

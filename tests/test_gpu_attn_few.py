@@ -12,7 +12,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("M,n_old,H,layers,out", [
     (1, 1, 1, 1, "f32"), (1, 30, 3, 1, "bf16"), (1, 31, 1, 2, "f32"), (1, 32, 1, 1, "f32"),   # one tile, ragged and full; two
     (15, 241, 2, 1, "f32"), (16, 240, 2, 1, "bf16"), (17, 240, 2, 2, "f32"),   # eight tiles: one a wave; one query of the next block
-    (1, 255, 1, 1, "f32"), (1, 256, 1, 1, "f32"),                   # the last size in one range, the first in two
+    (1, 479, 1, 1, "f32"), (1, 480, 1, 1, "f32"),                   # the last size in one range, the first in two
     (1, 4095, 1, 1, "f32"), (5, 4200, 3, 1, "bf16"),                # the most ranges; ranges of unequal length
     (33, 16000, 16, 1, "f32"), (64, 8000, 16, 1, "bf16"),           # two groups, the last one of padding; two full ones
     (128, 16384, 16, 1, "f32"), (97, 4096, 16, 12, "bf16"),         # four groups, split and not

@@ -165,7 +165,7 @@ def test_attention_route_follows_the_size_of_the_launch_and_of_the_device():
                     continue
                 assert r["workgroups"] == blocks * r["ranges"] <= max(blocks, n_wgs), (dtype, n_wgs, M, H, n, r)
                 assert r["ranges"] == 1 or blocks < n_wgs
-    for dtype, last in (("f32", 496), ("bf16", 256)):    # where the second range begins
+    for dtype, last in (("f32", 496), ("bf16", 480)):    # where the second range begins
         assert [route(1, 1, n, dtype=dtype)["ranges"] for n in (last, last + 1)] == [1, 2]
     # more blocks than compute units: ranges even out the last round of the device at hand
     assert route(272, 16, 1572, dtype="f32")["ranges"] == 1 and route(1041, 16, 5137, dtype="f32")["ranges"] > 1
