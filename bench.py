@@ -34,6 +34,7 @@ if ROOT not in sys.path:
 from paper_2603_05959_amd import synth  # noqa: E402
 
 MFMA_F16_PEAK_TFLOPS = 2500.0        # MI355X dense f16 / bf16 (same figure)
+MFMA_F32_PEAK_TFLOPS = 157.3         # f32 matrix units
 HBM_PEAK_GBS = 8000.0
 ARITHMETIC = "bf16 in/out, f16 MFMA (K, V and softmax weights as IEEE half), fp32 accumulate and softmax"
 
@@ -229,11 +230,14 @@ def run_workload(cfg, W, K, *, hybrid_beta=None, smooth_alpha=None, rising=False
     # from the committed rocprofv3 summary of this workload (stored-score ranking, no smoothing): HBM
     # bytes per launch, and the kernel's steady-state duration in the trace
     wl = cfg.name.split("-")[0]
-    traffic = profiled_figure("traffic_bytes_per_launch", "attn_bf16_kernel", wl, L)
+    kernel = {"items": "attn_bf16_kernel", "few": "attn_few_kernel", "f32": "attn_f32_kernel"}[
+        B.ovggt_attn_route(cache.cfg, L, n_keys, torch.cuda.get_device_properties(dev).multi_processor_count)["kernel"]]
+    traffic = profiled_figure("traffic_bytes_per_launch", kernel, wl, L)
     traffic = None if traffic is None else int(traffic)
-    trace_us = profiled_figure("trace_avg_kernel_us", "attn_bf16_kernel", wl, L)
-    roofline = {"bound": "mfma", "kernel": "attn_bf16_kernel", "achieved": achieved, "peak": MFMA_F16_PEAK_TFLOPS,
-                "unit": "TFLOP/s", "frac": achieved / MFMA_F16_PEAK_TFLOPS,
+    trace_us = profiled_figure("trace_avg_kernel_us", kernel, wl, L)
+    peak = MFMA_F16_PEAK_TFLOPS if cfg.dtype == "bf16" else MFMA_F32_PEAK_TFLOPS
+    roofline = {"bound": "mfma", "kernel": kernel, "achieved": achieved, "peak": peak,
+                "unit": "TFLOP/s", "frac": achieved / peak,
                 "traffic": traffic, "avg_kernel_ms": attn_avg_ms,
                 "profiled_kernel_ms": None if trace_us is None else trace_us * 1e-3, "event_bracket_ms": bracket_ms,
                 "event_bracket_of_empty_launch_ms": bracket_overhead_ms, "launches_timed": int(attn_cnt),
