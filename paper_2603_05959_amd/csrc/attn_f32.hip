@@ -12,11 +12,12 @@
 // enter the matrix unit from these registers; no operand passes through LDS.
 //
 // 1041 queries over 5137 slots, 16 heads (22 GFLOP): 39.5 ms as a scalar kernel with
-// one workgroup per query, 225 us like this, 97 TFLOP/s; the f32 matrix rate (157
-// at 2.4 GHz) bounds it: the matrix pipes are busy 60 % of the time, and what they
-// wait for is K and V out of L2 (11 TB/s: a 16-query block re-reads both).  Blocks of
-// 32 queries halve that traffic but fill the chip worse (528 instead of 1056 blocks
-// for 256 CUs) and took 10 to 20 % longer over every size from 17 to 1041 queries.
+// one workgroup per query, 230 us like this (a step of 253 us less 23 of append and
+// selection; 254 under a trace), 95 TFLOP/s; the f32 matrix rate (157 at 2.4 GHz)
+// bounds it: the matrix pipes are busy 60 % of the time, and what they wait for is K
+// and V out of L2 (11 TB/s: a 16-query block re-reads both).  Blocks of 32 queries
+// halve that traffic but fill the chip worse (528 instead of 1056 blocks for 256 CUs)
+// and took 10 to 20 % longer over every size from 17 to 1041 queries.
 #include "attn_parts.h"
 #include <type_traits>
 
