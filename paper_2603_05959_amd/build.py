@@ -8,7 +8,7 @@ import sys
 PKG = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libovggt.so")
-SOURCES = ["ovggt_api.cpp", "dap_policy.cpp", "cache_kernels.hip", "select_kernels.hip", "hybrid_kernels.hip", "attn_f32.hip", "attn_few.hip", "attn_bf16.hip"]
+SOURCES = ["ovggt_api.cpp", "dap_policy.cpp", "cache_kernels.hip", "select_kernels.hip", "select_wide.hip", "hybrid_kernels.hip", "attn_f32.hip", "attn_few.hip", "attn_bf16.hip"]
 MEASURE_LIB = os.path.join(PKG, "libovggt_measure.so")       # measurement helper, a library of its own
 MEASURE_SOURCES = ["measure/mfma_loop.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

@@ -86,6 +86,7 @@ void make_geom(const ovggt_config& c, Geom* g) {
   g->off_dval = off;  off += c.score_mode == 1 ? up256((size_t)4 * g->cap) : 0;
   g->off_dpart = off; off += c.score_mode == 1 ? up256((size_t)8 * kDivWavesPerWg * diversity_grid_x(g->cap, 1)) : 0;
   g->off_mvmap = off; off += up256((size_t)4 * g->M);
+  g->off_raw = off;   off += up256((size_t)8 * g->M);
   g->off_hist = off;  off += up256((size_t)4 * kSelHistBins);
   g->off_arrive = off; off += up256((size_t)4 * std::min<int64_t>(kMaxArrive, (int64_t)g->H * ((g->M + 15) / 16)));
   g->hybrid = c.score_mode == 1 ? 1 : 0;

@@ -23,10 +23,12 @@ constexpr int kMaxAttnWgs = 256;    // upper bound on attention workgroups (one 
 struct Ctrl {
   uint32_t status;     // OVGGT_STATUS_* bits
   uint32_t n_moves;    // length of the move list written by the last selection
-  uint32_t arrive;     // arrival counter of the score kernel's workgroups
+  uint32_t arrive;     // arrival counter of the workgroups of a score launch (select_wide.hip)
+  uint32_t done;       // workgroups of a score launch that have ended: zero between launches
   uint32_t gid_next;   // token id of the next frame's first token (t * M): read by the append, advanced by M by
                        // the frame's selection, so a step's launches carry no per-frame argument
-  uint32_t pad[60];
+  uint32_t launches;   // score launches that have ended; one more is the tag of the scores of the launch that runs
+  uint32_t pad[58];
 };
 static_assert(sizeof(Ctrl) == 256, "Ctrl is one 256-byte block");
 
@@ -47,8 +49,9 @@ struct Geom {
   size_t off_cvec;         // the sum as H*d fp32 values, refreshed by each frame's append (hybrid scoring)
   size_t off_dpart;        // (min, max) of d_i over the evictable slots of each wave of the diversity pass (hybrid scoring)
   size_t off_mvmap;        // per slot B + j (j < M): the slot below B it moves to under the last selection, or kNoMove
-  size_t off_hist;         // kSelHistBins counters: the selection's first-level histogram of the cached entries' score
-                           // words, filled by all workgroups of a launch and zeroed again by the one that selects
+  size_t off_raw;          // the new frame's scores on their way from the workers to the selecting workgroup: M pairs (score, tag)
+  size_t off_hist;         // kSelHistBins counters: the selection's first-level histogram of the cached entries' score words
+                           // (select_wide.hip), filled by all workgroups of a launch and zeroed again by the one that selects
   size_t off_arrive;       // up to kMaxArrive counters of finished parts, one per (head, block of queries) whose slots several
                            // workgroups share (attn_parts.h): zero between launches, so not in the workspace, whose contents
                            // no launch may count on
@@ -154,6 +157,10 @@ hipError_t launch_centroid_rebuild(const Geom& g, char* kv, char* meta, int laye
 // move list.
 hipError_t launch_score_select(const Geom& g, const SmoothParams& sm, const HybridParams& hy, char* meta, int layer0, int nl, const void* resid,
                                const uint8_t* anchors, int n_total, hipStream_t s);
+
+// The same for caches and frames beyond what its kernel holds on one CU.
+hipError_t launch_score_select_wide(const Geom& g, const SmoothParams& sm, const HybridParams& hy, char* meta, int layer0, int nl,
+                                    const void* resid, const uint8_t* anchors, int n_total, int n_cus, hipStream_t s);
 
 // Sec. 3.3: set or clear the protection flag of the resident tokens with ids in [gid_lo, gid_lo + M) whose mask
 // byte is set (mask may be null: all).  launch_centroid_protect adjusts the hybrid-scoring sum for the same change

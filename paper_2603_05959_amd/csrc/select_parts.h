@@ -1,0 +1,502 @@
+// What the two selection kernels share: the scores of the frame's rows, activation smoothing, the steps of a
+// histogram or radix selection by one workgroup, and the move list.  `Shared` is a kernel's LDS: SelCommon, the
+// bitmap evmap() and kRadixWords words radix() for the streaming selection.
+#pragma once
+#include "ovggt_internal.h"
+#include "../../include/ovggt.h"
+
+namespace ovggt {
+
+constexpr int kSelThreads = 1024;
+constexpr int kSelWaves = kSelThreads / 64;
+constexpr int kMaxSelChunks = 128;           // n_total <= 128 * 1024 slots
+
+// A barrier for what the workgroup shares in LDS: it doesn't wait for loads and stores of memory, each of which would
+// cost a round trip.  Where threads hand each other anything in memory, __syncthreads().
+__device__ inline void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+// Wave-wide scans and sums on lane permutes of the vector unit (a few cycles a step where a shuffle through LDS takes a hundred).
+template <int CTRL, int ROWS = 0xF>
+__device__ inline uint32_t lanes_moved(uint32_t old, uint32_t x) {
+  return (uint32_t)__builtin_amdgcn_update_dpp((int)old, (int)x, CTRL, ROWS, 0xF, false);
+}
+__device__ inline uint32_t wave_scan(uint32_t x) {       // inclusive
+  x += lanes_moved<0x111>(0u, x);                        // 1, 2, 4, 8 lanes up within a row of 16
+  x += lanes_moved<0x112>(0u, x);
+  x += lanes_moved<0x114>(0u, x);
+  x += lanes_moved<0x118>(0u, x);
+  x += lanes_moved<0x142, 0xA>(0u, x);                   // the last lane of rows 0 and 2 to the row behind it
+  x += lanes_moved<0x143, 0xC>(0u, x);                   // lane 31 to the upper half
+  return x;
+}
+// Of 16 values, one a wave, in LDS: their sum and the sum of those in front of this wave (uniform).
+__device__ inline void waves_scan(const uint32_t* of_waves, int stride, int wave, uint32_t* before, uint32_t* total) {
+  uint32_t x = of_waves[(threadIdx.x & 15) * stride];
+  x += lanes_moved<0x111>(0u, x);
+  x += lanes_moved<0x112>(0u, x);
+  x += lanes_moved<0x114>(0u, x);
+  x += lanes_moved<0x118>(0u, x);
+  *before = wave > 0 ? (uint32_t)__builtin_amdgcn_readlane((int)x, wave - 1) : 0u;
+  *total = (uint32_t)__builtin_amdgcn_readlane((int)x, 15);
+}
+template <typename F>
+__device__ inline float wave_fold(float x, F f) {        // a balanced tree over neighbouring lanes, f commutative; the same in every lane
+  auto step = [&](uint32_t y) { x = f(x, __uint_as_float(y)); };
+  const auto b = [&] { return __float_as_uint(x); };
+  step(lanes_moved<0xB1>(b(), b()));                     // neighbours, pairs, quads, eights
+  step(lanes_moved<0x4E>(b(), b()));
+  step(lanes_moved<0x141>(b(), b()));
+  step(lanes_moved<0x140>(b(), b()));
+  auto r = __builtin_amdgcn_permlane16_swap(b(), b(), false, false);
+  x = f(__uint_as_float(r[0]), __uint_as_float(r[1]));
+  r = __builtin_amdgcn_permlane32_swap(b(), b(), false, false);
+  return f(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+
+__device__ inline float bf16_to_f32(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
+
+// ---- scores of the frame's rows ---------------------------------------------
+// Sum of squares of elements [first, first + E) of a row as a balanced tree over neighbours; elements from C on count
+// as zeros.
+template <int E, bool BF16>
+__device__ inline float lane_sum_sq(const char* row, int C, int first) {
+  if constexpr (E > 16) {
+    const float lo = lane_sum_sq<E / 2, BF16>(row, C, first);
+    return __fadd_rn(lo, lane_sum_sq<E / 2, BF16>(row, C, first + E / 2));
+  }
+  float p[E];
+  if constexpr (BF16) {
+    const uint16_t* r = (const uint16_t*)row;
+    if constexpr (E >= 8) {
+      if ((C & 7) == 0) {
+#pragma unroll
+        for (int j = 0; j < E; j += 8) {
+          uint4 w = {0u, 0u, 0u, 0u};
+          if (first + j < C) w = *(const uint4*)(r + first + j);
+          const uint32_t ww[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+          for (int t = 0; t < 4; ++t) {
+            const float a = __uint_as_float(ww[t] << 16), b = __uint_as_float(ww[t] & 0xFFFF0000u);
+            p[j + 2 * t] = __fmul_rn(a, a);
+            p[j + 2 * t + 1] = __fmul_rn(b, b);
+          }
+        }
+        goto tree;
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < E; ++j) {
+      const float a = (first + j < C) ? bf16_to_f32(r[first + j]) : 0.f;
+      p[j] = __fmul_rn(a, a);
+    }
+  } else {
+    const float* r = (const float*)row;
+    if constexpr (E >= 4) {
+      if ((C & 3) == 0) {
+#pragma unroll
+        for (int j = 0; j < E; j += 4) {
+          float4 w = {0.f, 0.f, 0.f, 0.f};
+          if (first + j < C) w = *(const float4*)(r + first + j);
+          p[j] = __fmul_rn(w.x, w.x); p[j + 1] = __fmul_rn(w.y, w.y);
+          p[j + 2] = __fmul_rn(w.z, w.z); p[j + 3] = __fmul_rn(w.w, w.w);
+        }
+        goto tree;
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < E; ++j) {
+      const float a = (first + j < C) ? r[first + j] : 0.f;
+      p[j] = __fmul_rn(a, a);
+    }
+  }
+tree:
+#pragma unroll
+  for (int w = 1; w < E; w *= 2)
+#pragma unroll
+    for (int j = 0; j < E; j += 2 * w) p[j] = __fadd_rn(p[j], p[j + w]);
+  return p[0];
+}
+
+template <int E, bool BF16>
+__device__ inline float row_sum_sq(const char* row, int C, int lane) {
+  int first = lane * E;
+  asm volatile("" : "+v"(first));              // the comparisons with C belong to the row: kept for all rows they spill
+  // each step adds the sum of the neighbouring group, which all of that group's lanes hold
+  return wave_fold(lane_sum_sq<E, BF16>(row, C, first), [](float x, float y) { return __fadd_rn(x, y); });
+}
+
+// Rows [first, end) of the frame, R consecutive ones per wave and round, by workgroup blk of n_blk.  The loads of
+// a wave's rows are independent, so all of them are in flight before the first reduction.  R = 1 spreads a single
+// layer's rows over as many CUs as possible, R = kRowsPerWave amortises a workgroup's arrival when the launch covers
+// many layers.
+// `put(token, score)` takes them: every lane holds every row's sum after the butterfly, lane r passes on row r, so the
+// wave's R consecutive scores leave in one instruction.
+template <int E, bool BF16, int R, typename Put>
+__device__ inline void score_rows(const char* rbase, size_t row_bytes, int C, int first, int end, int blk, int n_blk, Put put) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  for (int tok0 = first + (blk * kSelWaves + wave) * R; tok0 < end; tok0 += n_blk * kSelWaves * R) {
+    float v[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+      v[r] = row_sum_sq<E, BF16>(rbase + (size_t)min(tok0 + r, end - 1) * row_bytes, C, lane);
+    float mine = v[0];
+#pragma unroll
+    for (int r = 1; r < R; ++r) mine = lane == r ? v[r] : mine;
+    if (lane < R && tok0 + lane < end) put(tok0 + lane, mine);
+  }
+}
+
+// Elements per lane: the tree is the same for every E that covers the row (the padding adds zeros), so three do.
+template <bool BF16, int R, typename Put>
+__device__ inline void score_rows_any(int e_per_lane, const char* rbase, size_t row_bytes, int C, int first, int end, int blk, int n_blk, Put put) {
+  if (e_per_lane <= 16) score_rows<16, BF16, R>(rbase, row_bytes, C, first, end, blk, n_blk, put);
+  else if (e_per_lane <= 32) score_rows<32, BF16, (R < 4 ? R : 4)>(rbase, row_bytes, C, first, end, blk, n_blk, put);
+  else score_rows<64, BF16, (R < 2 ? R : 2)>(rbase, row_bytes, C, first, end, blk, n_blk, put);
+}
+
+// ---- activation smoothing (Eq. 6), by the selecting workgroup ------------------------------
+// s = sqrt(ss) for every new token; patch tokens (row-major ph x pw map behind the n_special aux
+// tokens) become alpha * (G * S) + (1 - alpha) * S with the border replicated, aux tokens keep s.
+// The result replaces ss as the token's rank key.  fp32 throughout, every operation rounded on its
+// own (contraction off, sqrtf is the correctly rounded one: the hardware's approximate square root
+// is a unit in the last place off now and then), taps added left to right in kernel order: the CPU
+// reference repeats exactly this sequence.  raw: s of the whole frame.
+__device__ inline float smoothed_score(const SmoothParams& sm, const float* raw, int i) {
+#pragma clang fp contract(off)
+  float v = raw[i];
+  if (i >= sm.n_special) {
+    const int p = i - sm.n_special, y = p / sm.pw, x = p - y * sm.pw;
+    float conv = 0.f;
+#pragma unroll
+    for (int t = 0; t < 9; ++t) {
+      const int yy = min(max(y + t / 3 - 1, 0), sm.ph - 1), xx = min(max(x + t % 3 - 1, 0), sm.pw - 1);
+      const float prod = sm.g[t] * raw[sm.n_special + yy * sm.pw + xx];
+      conv = t == 0 ? prod : conv + prod;
+    }
+    const float blur = sm.alpha * conv, keep = (1.0f - sm.alpha) * v;
+    v = blur + keep;
+  }
+  return v;
+}
+
+// ---- selection: shared state ---------------------------------------------------
+constexpr int kHoleListCap = kSelHistBins;   // hole-list entries mirrored in LDS (longer lists are read back from memory)
+constexpr int kFinalCap = 64;        // keys that still tie after the second level: ordered by one wave
+constexpr int kRadixWords = 128 * 64;
+struct SelCommon {
+  uint32_t level0[kSelHistBins + 64];   // first-level counts; then the moves' prefix, per bitmap word of the new frame
+  uint32_t level1[kSelHistBins];     // second-level counts; then the first entries of the hole list
+  uint32_t cnt[256];
+  uint32_t scan_tmp[2 * kSelWaves];
+  uint32_t digit, rank, bucket, n_evictable, bad;
+};
+static_assert(kSelHistBins + 64 >= (1 << 16) / 32 + 2, "a prefix per bitmap word of the new frame");
+
+constexpr uint32_t kNotEvictable = 0xFFFFFFFFu;   // score word of protected / absent slots (no real score maps to it)
+
+// Score word of a slot: the fp32 bit pattern of ss (order-preserving for ss >= 0);
+// NaN or negative values rank lowest (0) and are reported.
+__device__ inline uint32_t score_word(float ss, bool* bad) {
+  const uint32_t b = __float_as_uint(ss);
+  const bool odd = b > 0x7F800000u;
+  *bad = *bad | odd;
+  return odd ? 0u : b;
+}
+
+// From the 256 bin counts in sh.cnt: the digit whose bucket holds the rank-th smallest candidate
+// (sh.digit), the rank inside that bucket (sh.rank), the bucket's size (sh.bucket) and the number
+// of candidates (sh.n_evictable).  Ends with a barrier.
+template <typename Shared>
+__device__ inline void pick_digit(Shared& sh, uint32_t rank) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  if (wave == 0) {
+    uint32_t c4[4];
+    uint32_t s = 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) { c4[j] = sh.cnt[4 * lane + j]; s += c4[j]; }
+    uint32_t inc = s;
+#pragma unroll
+    for (int off = 1; off < 64; off *= 2) {
+      const uint32_t y = __shfl_up(inc, off, 64);
+      if (lane >= off) inc += y;
+    }
+    uint32_t before = inc - s;
+    if (lane == 63) sh.n_evictable = inc;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      if (before < rank && rank <= before + c4[j]) {
+        sh.digit = 4 * lane + j; sh.rank = rank - before; sh.bucket = c4[j];
+      }
+      before += c4[j];
+    }
+  }
+  __syncthreads();
+}
+
+// One radix pass of the streaming selection (keys re-read from memory): histogram of an 8-bit digit
+// of the candidates (digit_of(chunk) < 0: not a candidate), then the digit whose bucket holds the
+// rank-th smallest candidate.  Results in sh.digit / sh.rank / sh.bucket (and sh.n_evictable =
+// number of candidates).
+template <typename Shared, typename DigitOf>
+__device__ inline void radix_pass(Shared& sh, int n_iter, uint32_t rank, DigitOf digit_of) {
+  const int tid = threadIdx.x, lane = tid & 63;
+  uint32_t (*hist)[64] = (uint32_t (*)[64])sh.radix();
+  for (int i = tid; i < kRadixWords; i += kSelThreads) (&hist[0][0])[i] = 0u;
+  __syncthreads();
+  // digits of 8 chunks are fetched together so their loads overlap
+  for (int c0 = 0; c0 < n_iter; c0 += 8) {
+    int dg[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) dg[j] = c0 + j < n_iter ? digit_of(c0 + j) : -1;
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      if (dg[j] >= 0) atomicAdd(&hist[dg[j] >> 1][lane], 1u << (16 * (dg[j] & 1)));
+  }
+  __syncthreads();
+  {   // column sums: thread -> (bin, quarter of the 64 columns)
+    const int bin = tid >> 2, quarter = tid & 3;
+    uint32_t s = 0;
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+      const int col = quarter * 16 + ((j + (lane >> 2)) & 15);   // 64 distinct columns per wave read
+      s += (hist[bin >> 1][col] >> (16 * (bin & 1))) & 0xFFFFu;
+    }
+    s += __shfl_xor(s, 1, 64);
+    s += __shfl_xor(s, 2, 64);
+    if (quarter == 0) sh.cnt[bin] = s;
+  }
+  __syncthreads();
+  pick_digit(sh, rank);
+}
+
+// timing builds leave 10 ns timestamps of the phases in the control block's padding
+#ifdef OVGGT_TRACE
+#define TSTAMP(k) do { if (tid == 0) ctrl->pad[k] = (uint32_t)wall_clock64(); } while (0)
+#else
+#define TSTAMP(k) do { } while (0)
+#endif
+
+// The ordered move list from the evict bitmap in sh.evmap() (complete, and a barrier behind it),
+// and the same moves keyed by source: mvmap[j] = destination of the entry in slot B + j, or
+// kNoMove (read by the append that applies an outstanding compaction).
+// Holes (evicted slots below B) and movers (kept slots from B on) are counted by 32-slot words of the
+// bitmap, a few consecutive words a thread; one scan over both counts gives a thread the list position of its
+// first hole and a word its number of movers before it.  The r-th mover then looks its destination up
+// in the hole list.
+template <typename Shared>
+__device__ inline void emit_moves(Shared& sh, const Geom& g, Ctrl* ctrl, uint32_t* mvdst, uint32_t* mvsrc,
+                                  uint32_t* mvmap, uint32_t* evbits, int n_total, bool budget_error, int pass) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  (void)pass;
+  uint32_t* movers_before = sh.level0;                     // per word from the one that holds slot B
+  const int n_words = (n_total + 31) >> 5;
+  if (evbits)
+    for (int wi = tid; wi < n_words; wi += kSelThreads) evbits[wi] = sh.evmap()[wi];
+  const uint32_t m_cap = (uint32_t)g.M;
+  const int hole_words = (g.B + 31) >> 5, first_word = g.B >> 5, mover_words = n_words - first_word;
+  const int PH = (hole_words + kSelThreads - 1) / kSelThreads, PM = (mover_words + kSelThreads - 1) / kSelThreads;   // <= 4, <= 3
+  auto hole_bits = [&](int wi) -> uint32_t {
+    const uint32_t below_b = (wi << 5) + 32 <= g.B ? 0xFFFFFFFFu : ((1u << (g.B & 31)) - 1u);
+    return budget_error ? 0u : sh.evmap()[wi] & below_b;
+  };
+  auto mover_bits = [&](int wi) -> uint32_t {
+    uint32_t in = 0xFFFFFFFFu;
+    if (wi == first_word) in &= ~((1u << (g.B & 31)) - 1u);
+    if ((wi << 5) + 32 > n_total) in &= (1u << (n_total & 31)) - 1u;
+    return budget_error ? 0u : ~sh.evmap()[wi] & in;
+  };
+  uint32_t nh = 0, nm = 0;
+  for (int j = 0; j < PH; ++j) {
+    const int wi = tid * PH + j;
+    if (wi < hole_words) nh += __popc(hole_bits(wi));
+  }
+  for (int j = 0; j < PM; ++j) {
+    const int wi = tid * PM + j;
+    if (wi < mover_words) nm += __popc(mover_bits(first_word + wi));
+  }
+  const uint32_t inc_h = wave_scan(nh), inc_m = wave_scan(nm);
+  if (lane == 63) ((uint2*)sh.scan_tmp)[wave] = uint2{inc_h, inc_m};
+  lds_barrier();
+  uint32_t base_h, tot_h, base_m, tot_m;
+  waves_scan(sh.scan_tmp, 2, wave, &base_h, &tot_h);
+  waves_scan(sh.scan_tmp + 1, 2, wave, &base_m, &tot_m);
+  uint32_t hp = base_h + inc_h - nh, mb = base_m + inc_m - nm;
+  for (int j = 0; j < PH; ++j) {                                 // the hole list (entries beyond M are never used)
+    const int wi = tid * PH + j;
+    if (wi >= hole_words) break;
+    uint32_t b = hole_bits(wi);
+    while (b) {
+      const uint32_t hole = ((uint32_t)wi << 5) + (uint32_t)__builtin_ctz(b);
+      if (hp < (uint32_t)kHoleListCap) sh.level1[hp] = hole;
+      else if (hp < m_cap) mvdst[hp] = hole;
+      ++hp; b &= b - 1;
+    }
+  }
+  for (int j = 0; j < PM; ++j) {
+    const int wi = tid * PM + j;
+    if (wi >= mover_words) break;
+    movers_before[wi] = mb;
+    mb += __popc(mover_bits(first_word + wi));
+  }
+  if (tot_h > (uint32_t)kHoleListCap) __syncthreads();           // some are read back from memory
+  else lds_barrier();
+  const bool consistent = !budget_error && tot_h == tot_m && tot_h <= m_cap;    // otherwise nothing moves
+  for (uint32_t i = tid; i < min(tot_h, min(m_cap, (uint32_t)kHoleListCap)); i += kSelThreads) mvdst[i] = sh.level1[i];
+  for (int slot = g.B + tid; slot < g.B + g.M; slot += kSelThreads) {
+    uint32_t to = kNoMove;
+    if (slot < n_total) {
+      const int wi = slot >> 5;
+      const uint32_t bits = mover_bits(wi), bit = 1u << (slot & 31);
+      if (bits & bit) {
+        const uint32_t mp = movers_before[wi - first_word] + __popc(bits & (bit - 1u));
+        if (mp < m_cap) mvsrc[mp] = (uint32_t)slot;
+        if (consistent) to = mp < (uint32_t)kHoleListCap ? sh.level1[mp] : mvdst[mp];
+      }
+    }
+    mvmap[slot - g.B] = to;
+  }
+  if (tid == 0) {
+    ctrl->n_moves = consistent ? tot_h : 0u;
+    uint32_t st = 0;
+    if (!consistent) st |= OVGGT_STATUS_BUDGET;
+    if (sh.bad) st |= OVGGT_STATUS_NONFINITE;
+    if (st) atomicOr(&ctrl->status, st);
+    TSTAMP(12);
+    OVGGT_TRACE_ONLY(ctrl->pad[13] = (uint32_t)pass;)
+  }
+}
+
+// Streaming radix selection by one workgroup, for any population of keys: 8-bit digits of the
+// 64-bit key (score word, inverted id), every pass re-reads the score words (and, once equal
+// scores straddle the threshold, the ids) from memory; passes stop as soon as a whole bucket goes.
+// The histogram selection falls back to it when its lists overflow.
+template <typename Shared>
+__device__ inline void select_streaming(Shared& sh, const Geom& g, const float* ss, const uint32_t* ids,
+                                        const uint8_t* flags, Ctrl* ctrl, uint32_t* mvdst, uint32_t* mvsrc,
+                                        uint32_t* mvmap, uint32_t* evbits, int n_total) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int n_chunks = (n_total + kSelThreads - 1) / kSelThreads;
+  const uint32_t n_evict = (uint32_t)(n_total - g.B);
+  bool bad = false;
+  auto word = [&](int c) -> uint32_t {               // branch-free so that loads of several chunks overlap
+    const int i = c * kSelThreads + tid;
+    const int ic = i < n_total ? i : n_total - 1;
+    const uint8_t f = flags[ic];
+    const uint32_t w = score_word(ss[ic], &bad);
+    return (i >= n_total || f != 0) ? kNotEvictable : w;
+  };
+  auto idw = [&](int c) -> uint32_t {
+    const int i = c * kSelThreads + tid;
+    return 0xFFFFFFFFu - ids[i < n_total ? i : n_total - 1];
+  };
+  TSTAMP(1);
+
+  // radix select of the n_evict-th smallest (score word, inverted id) pair
+  uint32_t rank = n_evict;
+  int pass = 0;
+  bool budget_error = false, done = false;
+  uint32_t pre_hi = 0, pre_lo = 0;
+#pragma nounroll
+  for (; pass < 4 && !done; ++pass) {
+    const int shift = 24 - 8 * pass;
+    radix_pass(sh, n_chunks, rank, [&](int c) -> int {
+      const uint32_t w = word(c);
+      if (w == kNotEvictable) return -1;
+      if (pass > 0 && (w >> (shift + 8)) != (pre_hi >> (shift + 8))) return -1;
+      return (int)((w >> shift) & 255u);
+    });
+    if (pass == 0 && sh.n_evictable < n_evict) { budget_error = true; break; }   // |P| > B
+    pre_hi |= sh.digit << shift;
+    rank = sh.rank;
+    done = (rank == sh.bucket);          // the whole bucket goes
+    __syncthreads();
+  }
+  const int hi_shift = pass > 0 ? 24 - 8 * (pass - 1) : 24;
+  int lo_shift = 32;                      // 32: ids did not have to be consulted
+  if (!done && !budget_error) {
+#pragma nounroll
+    for (int p2 = 0; p2 < 4 && !done; ++p2) {
+      const int shift = 24 - 8 * p2;
+      radix_pass(sh, n_chunks, rank, [&](int c) -> int {
+        if (word(c) != pre_hi) return -1;
+        const uint32_t w = idw(c);
+        if (p2 > 0 && (w >> (shift + 8)) != (pre_lo >> (shift + 8))) return -1;
+        return (int)((w >> shift) & 255u);
+      });
+      pre_lo |= sh.digit << shift;
+      rank = sh.rank;
+      done = (rank == sh.bucket);
+      lo_shift = shift;
+      __syncthreads();
+    }
+  }
+  TSTAMP(7);
+  if (bad) sh.bad = 1;
+
+  // evict bit per slot, published in slot order: the ballot of one chunk over one wave covers 64
+  // consecutive slots
+  for (int c = 0; c < n_chunks; ++c) {
+    bool ev = false;
+    if (!budget_error) {
+      const uint32_t w = word(c);
+      if (w != kNotEvictable) {
+        if (lo_shift == 32) ev = (w >> hi_shift) <= (pre_hi >> hi_shift);
+        else ev = w < pre_hi || (w == pre_hi && (idw(c) >> lo_shift) <= (pre_lo >> lo_shift));
+      }
+    }
+    const uint64_t bl = __ballot(ev);
+    if (lane == 0) {
+      sh.evmap()[(c * kSelThreads >> 5) + 2 * wave] = (uint32_t)bl;
+      sh.evmap()[(c * kSelThreads >> 5) + 2 * wave + 1] = (uint32_t)(bl >> 32);
+    }
+  }
+  __syncthreads();
+  TSTAMP(11);
+  emit_moves(sh, g, ctrl, mvdst, mvsrc, mvmap, evbits, n_total, budget_error, pass);
+}
+
+// Inclusive scan over the 2 * 1024 bin counts (thread t owns bins 2t and 2t+1): the bin that holds
+// the rank-th smallest key (sh.digit), the rank inside it (sh.rank), its size (sh.bucket) and the
+// total (sh.n_evictable).  rank > total leaves the first three unwritten.  Ends with a barrier.
+template <typename Shared>
+__device__ inline void pick_bin(Shared& sh, const uint32_t* counts, uint32_t rank) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const uint2 c = ((const uint2*)counts)[tid];
+  const uint32_t s = c.x + c.y;
+  const uint32_t inc = wave_scan(s);
+  if (lane == 63) sh.scan_tmp[wave] = inc;
+  lds_barrier();
+  uint32_t base, tot;
+  waves_scan(sh.scan_tmp, 1, wave, &base, &tot);
+  uint32_t before = base + inc - s;
+  if (before < rank && rank <= before + c.x) { sh.digit = 2 * tid; sh.rank = rank - before; sh.bucket = c.x; }
+  before += c.x;
+  if (before < rank && rank <= before + c.y) { sh.digit = 2 * tid + 1; sh.rank = rank - before; sh.bucket = c.y; }
+  if (tid == 0) sh.n_evictable = tot;
+  lds_barrier();
+}
+
+// Minimum and maximum over the workgroup.
+template <typename Shared>
+__device__ inline void block_min_max(Shared& sh, float* lo_io, float* hi_io) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const float lo = wave_fold(*lo_io, [](float x, float y) { return fminf(x, y); });
+  const float hi = wave_fold(*hi_io, [](float x, float y) { return fmaxf(x, y); });
+  float* red = (float*)sh.cnt;                               // 2 values per wave
+  if (lane == 0) { red[wave * 2] = lo; red[wave * 2 + 1] = hi; }
+  lds_barrier();
+  *lo_io = wave_fold(red[(lane & 15) * 2], [](float x, float y) { return fminf(x, y); });
+  *hi_io = wave_fold(red[(lane & 15) * 2 + 1], [](float x, float y) { return fmaxf(x, y); });
+  lds_barrier();                                             // sh.cnt is reused afterwards
+}
+
+// Eq. 7: a source's value, min-max normalised over its evictable slots (all zeros when max = min) and weighted,
+// (1 - beta) * d^ for history, beta * s^ for the new frame.  One fp32 operation at a time, in this order; the CPU
+// reference repeats it.
+__device__ inline float rank_value(float x, float lo, float hi, float weight) {
+#pragma clang fp contract(off)
+  const float unit = hi == lo ? 0.f : (x - lo) / (hi - lo);
+  return weight * unit;
+}
+
+}  // namespace ovggt

@@ -1,0 +1,418 @@
+// The selection of select_kernels.hip for caches whose score words do not fit one CU's LDS, and for frames of thousands of
+// tokens: here every workgroup counts a share of the cached entries, and the one that arrives last selects.
+//
+// Phase 1 (all workgroups): one wave per new token reduces the token's residual row.  While its rows load, every
+// workgroup also counts its share of the cached entries by the 11 leading bits of their score words (LDS histogram,
+// flushed to per-layer counters in memory with one device-scope atomic per occupied bin).
+//
+// Phase 2 (the workgroup that arrives last for a layer, found with an arrival
+// counter; nobody waits): if more than B entries are resident, find the E =
+// n - B lowest-ranked evictable entries: the counters give the
+// threshold's first-level bin, one pass over the score words marks what lies
+// below it and collects what lies in it, a second 11-bit level over those
+// candidates leaves a handful of keys that one wave orders (ids included).
+// Populations that defeat the two levels take a streaming 8-bit radix selection.
+#include "select_parts.h"
+
+namespace ovggt {
+
+// Tokens scored per wave and round when many layers are batched (one round covers 24 layers of 1374
+// rows with 10 workgroups each; measured 23 us with 4 rows in flight per wave, 19.5 us with 9,
+// 17.8 us once the wave's scores leave in one store instruction).
+constexpr int kRowsPerWave = 9;
+
+// Device-coherent (write-through) stores: the selection may run on another XCD, and a
+// device-scope release fence per workgroup (an L2 write-back each) would cost far more.
+struct PutCoherent {
+  const uint8_t* anchors;
+  float* ss;
+  uint8_t* flags;
+  __device__ void operator()(int i, float v) const {
+    __hip_atomic_store(&ss[i], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(&flags[i], (uint8_t)((anchors && anchors[i]) ? 1 : 0), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+};
+
+// Eq. 6 by the workgroup that saw all scores arrive; `raw` is scratch for M floats.
+__device__ inline void smooth_new_scores(const SmoothParams& sm, int M, float* key, float* raw) {
+  for (int i = threadIdx.x; i < M; i += kSelThreads) raw[i] = __builtin_sqrtf(key[i]);
+  __syncthreads();
+  for (int i = threadIdx.x; i < M; i += kSelThreads) key[i] = smoothed_score(sm, raw, i);
+  __syncthreads();
+}
+
+constexpr int kCandCap = 8192;     // candidates (keys in the threshold's first-level bin) held in LDS
+struct WideShared : SelCommon {
+  uint32_t cand[2 * kCandCap];     // score words and slots; streaming selection: its histogram columns
+  uint32_t evbits[kMaxSelChunks * kSelThreads / 32];  // evict bit per slot, slot order
+  uint32_t candmap[kMaxSelChunks * kSelThreads / 32]; // slots whose key lies in the threshold's bin
+  uint32_t is_last, n_cand, n_final;
+  uint32_t final_list[kFinalCap];  // candidate-list positions of the keys that the last wave step orders
+  __device__ uint32_t* evmap() { return evbits; }
+  __device__ uint32_t* radix() { return cand; }
+};
+
+// Every workgroup, before it announces its arrival, counts its share of the cached entries
+// [0, n_old) by first-level bin into `lh` (LDS, zero, a barrier behind the clearing).  Protected
+// entries do not take part.  The share's first two entries per thread are requested before the
+// frame's rows are scored (hist_share_load) and counted afterwards, so their latency hides there.
+struct HistShare { uint32_t w[2]; int next, end; };
+
+__device__ inline uint32_t evictable_word(float ssv, uint8_t flag) {
+  bool bad = false;                                     // bad scores are reported by the workgroup that selects
+  const uint32_t w = score_word(ssv, &bad);
+  return flag ? kNotEvictable : w;
+}
+
+__device__ inline HistShare hist_share_load(const float* ss, const uint8_t* flags, int n_old) {
+  HistShare h;
+  const int per = (n_old + (int)gridDim.x - 1) / (int)gridDim.x;
+  const int i0 = blockIdx.x * per + threadIdx.x;
+  h.end = min(((int)blockIdx.x + 1) * per, n_old);
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const int i = i0 + j * kSelThreads;
+    const int ic = min(i, n_old - 1);                   // n_old >= 1 whenever a selection runs
+    const uint32_t w = evictable_word(ss[ic], flags[ic]);
+    h.w[j] = i < h.end ? w : kNotEvictable;
+  }
+  h.next = i0 + 2 * kSelThreads;
+  return h;
+}
+
+__device__ inline void hist_share_count(uint32_t* lh, const HistShare& h, const float* ss, const uint8_t* flags) {
+#pragma unroll
+  for (int j = 0; j < 2; ++j)
+    if (h.w[j] != kNotEvictable) atomicAdd(&lh[h.w[j] >> 20], 1u);
+  for (int i = h.next; i < h.end; i += kSelThreads) {
+    const uint32_t w = evictable_word(ss[i], flags[i]);
+    if (w != kNotEvictable) atomicAdd(&lh[w >> 20], 1u);
+  }
+}
+
+// Adds the occupied bins of `lh` to the layer's counters and leaves `lh` zero (a barrier in front).
+__device__ inline void hist_flush(uint32_t* lh, uint32_t* ghist) {
+  __syncthreads();
+#pragma unroll
+  for (int b = threadIdx.x; b < kSelHistBins; b += kSelThreads) {
+    const uint32_t v = lh[b];
+    if (v) {
+      __hip_atomic_fetch_add(&ghist[b], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      lh[b] = 0u;
+    }
+  }
+}
+
+constexpr int kQuadBatch = 6;       // 16-byte score loads (4 slots each) a thread keeps in flight
+struct QuadBatch { float4 sv[kQuadBatch]; uint32_t fl[kQuadBatch]; };
+
+__device__ inline void select_hist(WideShared& sh, const Geom& g, const float* ss, const uint32_t* ids,
+                                   const uint8_t* flags, Ctrl* ctrl, uint32_t* mvdst, uint32_t* mvsrc,
+                                   uint32_t* mvmap, uint32_t* evbits, uint32_t* ghist, int n_total) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int n_old = n_total - g.M;
+  const uint32_t n_evict = (uint32_t)(n_total - g.B);
+  uint32_t* lh = sh.level0;                           // first level, zero on entry
+  uint32_t* h2 = sh.level1;                           // second level, zero on entry
+  uint32_t* cand_w = sh.cand;                    // candidates: score word and slot
+  uint32_t* cand_slot = cand_w + kCandCap;
+  bool bad = false;
+  TSTAMP(1);
+  // first level: the other workgroups' counts of the cached entries, plus the frame's own tokens
+  const uint2 gh = *(const uint2*)(ghist + 2 * tid);
+  const int n_quads = (n_total + 3) >> 2;
+  auto load_batch = [&](QuadBatch& qb, int q0) {
+#pragma unroll
+    for (int j = 0; j < kQuadBatch; ++j) {
+      const int q = min(q0 + j * kSelThreads + tid, n_quads - 1);
+      qb.sv[j] = ((const float4*)ss)[q];
+      qb.fl[j] = ((const uint32_t*)flags)[q];
+    }
+  };
+  QuadBatch qb0;
+  if (tid == 0) { sh.bad = 0; sh.n_cand = 0; sh.n_final = 0; }
+  for (int wi = tid; wi < (n_total + 31) >> 5; wi += kSelThreads) sh.evbits[wi] = sh.candmap[wi] = 0u;   // a barrier follows below
+  for (int i0 = n_old + tid; i0 < n_total; i0 += 2 * kSelThreads) {    // two loads in flight per thread
+    uint32_t w[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int i = i0 + j * kSelThreads;
+      const int ic = min(i, n_total - 1);
+      const uint32_t x = evictable_word(ss[ic], flags[ic]);
+      w[j] = i < n_total ? x : kNotEvictable;
+    }
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+      if (w[j] != kNotEvictable) atomicAdd(&lh[w[j] >> 20], 1u);
+  }
+  load_batch(qb0, 0);                                   // in flight while the bin is picked
+  __syncthreads();
+  lh[2 * tid] += gh.x; lh[2 * tid + 1] += gh.y;      // each thread's own
+  pick_bin(sh, lh, n_evict);
+  // the counters start the next frame at zero (written through; the values above are in registers)
+  __hip_atomic_store(&ghist[2 * tid], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __hip_atomic_store(&ghist[2 * tid + 1], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const bool budget_error = sh.n_evictable < n_evict;   // |P| > B
+  const uint32_t bin1 = sh.digit, rank1 = sh.rank;
+  const bool all1 = rank1 == sh.bucket;                 // the whole bin goes
+  TSTAMP(2);
+  // One pass over the score words, four consecutive slots per thread and load, in batches of
+  // kQuadBatch loads per thread; the next batch is requested before the current one is used (the
+  // first one before the bin was picked).  Two bitmaps: "below the bin" (w < thr_lo: the entry
+  // goes) and "in the bin" (thr_lo <= w < thr_hi: a candidate).  Protected and absent slots carry
+  // the all-ones word, which is neither.
+  const uint32_t thr_lo = budget_error ? 0u : (all1 ? bin1 + 1u : bin1) << 20;
+  const uint32_t thr_hi = (budget_error || all1) ? thr_lo : thr_lo + (1u << 20);   // at most 2^31
+  auto use_batch = [&](const QuadBatch& qb, int q0) {
+#pragma unroll
+    for (int j = 0; j < kQuadBatch; ++j) {
+      const int q = q0 + j * kSelThreads + tid;
+      if (q < n_quads) {
+        const int base = q << 2, n_valid = n_total - base;
+        uint32_t w[4] = {__float_as_uint(qb.sv[j].x), __float_as_uint(qb.sv[j].y), __float_as_uint(qb.sv[j].z),
+                         __float_as_uint(qb.sv[j].w)};
+        const uint32_t w_max = max(max(w[0], w[1]), max(w[2], w[3]));
+        if (qb.fl[j] != 0u || n_valid < 4 || w_max > 0x7F800000u) {   // rare: protected, tail, NaN or negative
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const bool in_range = e < n_valid;
+            const bool odd = w[e] > 0x7F800000u;        // ranks lowest, reported
+            if (odd && in_range) bad = true;
+            if (odd) w[e] = 0u;
+            if (!in_range || ((qb.fl[j] >> (8 * e)) & 255u) != 0u) w[e] = kNotEvictable;
+          }
+        }
+        uint32_t nib_lo = 0, nib_hi = 0;
+#pragma unroll
+        for (int e = 3; e >= 0; --e) {
+          nib_lo = 2u * nib_lo + (w[e] < thr_lo ? 1u : 0u);
+          nib_hi = 2u * nib_hi + (w[e] < thr_hi ? 1u : 0u);
+        }
+        const uint32_t sft = base & 31;
+        if (nib_lo) atomicOr(&sh.evbits[base >> 5], nib_lo << sft);
+        if (nib_hi != nib_lo) atomicOr(&sh.candmap[base >> 5], (nib_hi ^ nib_lo) << sft);
+      }
+    }
+  };
+  constexpr int kStep = kQuadBatch * kSelThreads;
+  for (int q0 = 0; q0 < n_quads; q0 += 2 * kStep) {
+    QuadBatch qb1;
+    if (q0 + kStep < n_quads) load_batch(qb1, q0 + kStep);          // uniform
+    use_batch(qb0, q0);
+    if (q0 + 2 * kStep < n_quads) load_batch(qb0, q0 + 2 * kStep);
+    if (q0 + kStep < n_quads) use_batch(qb1, q0 + kStep);
+  }
+  if (bad) sh.bad = 1;
+  __syncthreads();
+  TSTAMP(5);
+  // the candidates (few) to a list, with their score words, and counted by their next 11 bits
+  for (int wi = tid; wi < (n_total + 31) >> 5; wi += kSelThreads) {
+    uint32_t bits = sh.candmap[wi];
+    while (bits) {
+      const uint32_t slot = ((uint32_t)wi << 5) + (uint32_t)__builtin_ctz(bits);
+      bits &= bits - 1;
+      const uint32_t b = __float_as_uint(ss[slot]);
+      const uint32_t w = b > 0x7F800000u ? 0u : b;
+      const uint32_t pos = atomicAdd(&sh.n_cand, 1u);
+      if (pos < (uint32_t)kCandCap) { cand_w[pos] = w; cand_slot[pos] = slot; }
+      atomicAdd(&h2[(w >> 9) & (kSelHistBins - 1)], 1u);
+    }
+  }
+  __syncthreads();
+  TSTAMP(3);
+  const uint32_t n_cand = sh.n_cand;
+  bool fallback = n_cand > (uint32_t)kCandCap;
+  if (!fallback && n_cand > 0) {
+    // second level over the candidates (n_cand = the bin's size, rank1 of them go)
+    pick_bin(sh, h2, rank1);
+    const uint32_t bin2 = sh.digit, rank2 = sh.rank;
+    const bool all2 = rank2 == sh.bucket;
+    for (uint32_t e = tid; e < n_cand; e += kSelThreads) {
+      const uint32_t d2 = (cand_w[e] >> 9) & (kSelHistBins - 1), slot = cand_slot[e];
+      if (d2 < bin2 || (all2 && d2 == bin2)) atomicOr(&sh.evbits[slot >> 5], 1u << (slot & 31));
+      else if (d2 == bin2) {
+        const uint32_t pos = atomicAdd(&sh.n_final, 1u);
+        if (pos < (uint32_t)kFinalCap) sh.final_list[pos] = e;
+      }
+    }
+    __syncthreads();
+    TSTAMP(4);
+    const uint32_t n_final = sh.n_final;
+    fallback = n_final > (uint32_t)kFinalCap;
+    if (!fallback && n_final > 0 && wave == 0) {
+      // rank2 of these keys go: a key's position in the order is the number of smaller keys
+      uint32_t w = 0xFFFFFFFFu, inv = 0xFFFFFFFFu, slot = 0;
+      if ((uint32_t)lane < n_final) {
+        const uint32_t e = sh.final_list[lane];
+        w = cand_w[e]; slot = cand_slot[e];
+        inv = 0xFFFFFFFFu - ids[slot];
+      }
+      const uint64_t key = ((uint64_t)w << 32) | inv;
+      uint32_t below = 0;
+      for (uint32_t j = 0; j < n_final; ++j) {
+        const uint64_t kj = ((uint64_t)(uint32_t)__shfl((int)w, (int)j, 64) << 32) | (uint32_t)__shfl((int)inv, (int)j, 64);
+        below += kj < key ? 1u : 0u;
+      }
+      if ((uint32_t)lane < n_final && below < rank2) atomicOr(&sh.evbits[slot >> 5], 1u << (slot & 31));
+    }
+  }
+  if (fallback) {                                       // uniform: decided from shared counters behind a barrier
+    select_streaming(sh, g, ss, ids, flags, ctrl, mvdst, mvsrc, mvmap, evbits, n_total);
+    return;
+  }
+  __syncthreads();
+  TSTAMP(11);
+  emit_moves(sh, g, ctrl, mvdst, mvsrc, mvmap, evbits, n_total, budget_error, 2);
+}
+
+// ---- Eq. 7: rank values of the evictable slots ----------------------------------------------------
+// History side, spread over every workgroup of the layer's launch.  `dval` holds d_i of the slots
+// below n_old, `part` the (minimum, maximum) over the evictable slots of each wave of this
+// frame's diversity pass (both read-only here).  Every workgroup folds the few thousand pairs into
+// the same minimum and maximum (reading all d_i and flags instead, 80 KB per workgroup, made this
+// phase take 13.5 us instead of 4.8), then writes the rank values of its own share of slots over
+// their scores, written through like the scores of phase 1, and counts them by first-level bin
+// into `lh`, which is zero and has a barrier behind its clearing.
+__device__ inline void hybrid_history_values(WideShared& sh, const HybridParams& hy, const float* dval,
+                                             const float2* part, float* ss, const uint8_t* flags, int n_old,
+                                             uint32_t* lh) {
+#pragma clang fp contract(off)
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  float lo = __builtin_inff(), hi = -__builtin_inff();
+  for (int i = tid; i < hy.n_part; i += kSelThreads) {
+    const float2 p = part[i];
+    lo = fminf(lo, p.x); hi = fmaxf(hi, p.y);
+  }
+  block_min_max(sh, &lo, &hi);
+  const int per = (n_old + (int)gridDim.x - 1) / (int)gridDim.x;
+  const int i1 = min(((int)blockIdx.x + 1) * per, n_old);
+  for (int i = blockIdx.x * per + threadIdx.x; i < i1; i += kSelThreads) {
+    if (flags[i]) continue;
+    const float rv = rank_value(dval[i], lo, hi, 1.0f - hy.beta);
+    __hip_atomic_store(&ss[i], rv, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    bool bad = false;                                        // first-level count of this share
+    atomicAdd(&lh[score_word(rv, &bad) >> 20], 1u);
+  }
+}
+
+// New frame's side, by the workgroup that runs the selection: the slots [n_old, n_total) hold ss, or
+// Eq. 6's smoothed s.
+__device__ inline void hybrid_new_values(WideShared& sh, const HybridParams& hy, bool smoothed, float* ss,
+                                         const uint8_t* flags, int n_old, int n_total) {
+  float lo = __builtin_inff(), hi = -__builtin_inff();
+  float* sn = ss + n_old;
+  const uint8_t* fn = flags + n_old;
+  auto value_of = [&](int i) { return smoothed ? sn[i] : __builtin_sqrtf(sn[i]); };
+  for (int i = threadIdx.x; i < n_total - n_old; i += kSelThreads)
+    if (!fn[i]) { lo = fminf(lo, value_of(i)); hi = fmaxf(hi, value_of(i)); }
+  block_min_max(sh, &lo, &hi);
+  for (int i = threadIdx.x; i < n_total - n_old; i += kSelThreads)
+    if (!fn[i]) sn[i] = rank_value(value_of(i), lo, hi, hy.beta);
+  __syncthreads();
+}
+
+template <bool BF16>
+__global__ void __launch_bounds__(kSelThreads)
+score_select_wide_kernel(Geom g, SmoothParams sm, HybridParams hy, char* meta, int layer0, const char* resid, const uint8_t* anchors,
+                    int n_total, int e_per_lane) {
+  __shared__ WideShared sh;
+  const int layer = layer0 + blockIdx.y;
+  const int li = blockIdx.y;
+  char* mb = layer_meta(meta, g, layer);
+  uint32_t* ids = (uint32_t*)(mb + g.off_ids);
+  float* ss = (float*)(mb + g.off_ss);
+  uint8_t* flags = (uint8_t*)(mb + g.off_flags);
+  Ctrl* ctrl = (Ctrl*)(mb + g.off_ctrl);
+  const int tid = threadIdx.x;
+  const int n_old = n_total - g.M;
+
+  OVGGT_TRACE_ONLY(if (blockIdx.x == 0 && tid == 0) ctrl->pad[15] = (uint32_t)wall_clock64();)
+  // The two histogram levels start at zero in every workgroup (each counts its share of the cache
+  // into the first, and whichever selects uses both); cleared in the shadow of phase 1's loads.
+  const bool selecting = n_total > g.B;
+  HistShare share = {};
+  if (selecting) {
+    ((uint2*)sh.level0)[tid] = ((uint2*)sh.level1)[tid] = uint2{0u, 0u};
+    if (!hy.on) share = hist_share_load(ss, flags, n_old);     // used after the rows are scored
+  }
+  // ---- phase 1: scores and flags of the M new slots
+  {
+    const size_t row_bytes = (size_t)g.C * g.esize;
+    const char* rbase = resid + (size_t)li * g.M * row_bytes;
+    const uint8_t* al = anchors ? anchors + (size_t)li * g.M : nullptr;
+    float* sn = ss + n_old;
+    uint8_t* fn = flags + n_old;
+    const bool many = gridDim.x * kSelWaves < (unsigned)g.M;       // the launch packs several tokens per wave
+    const PutCoherent put = {al, sn, fn};
+    if (many) score_rows_any<BF16, kRowsPerWave>(e_per_lane, rbase, row_bytes, g.C, 0, g.M, blockIdx.x, gridDim.x, put);
+    else score_rows_any<BF16, 1>(e_per_lane, rbase, row_bytes, g.C, 0, g.M, blockIdx.x, gridDim.x, put);
+  }
+  // first histogram level of this workgroup's share of the cached entries, added to the layer's counters
+  uint32_t* lh = sh.level0;
+  uint32_t* ghist = (uint32_t*)(mb + g.off_hist);
+  if (selecting) {
+    if (hy.on)
+      hybrid_history_values(sh, hy, (const float*)(mb + g.off_dval), (const float2*)(mb + g.off_dpart), ss, flags, n_old, lh);
+    else {
+      __syncthreads();                         // the histogram was cleared when the kernel started
+      hist_share_count(lh, share, ss, flags);
+    }
+    hist_flush(lh, ghist);
+  }
+  const bool smoothing = sm.alpha > 0.f;
+  if (n_total <= g.B && !smoothing) {        // under budget and no smoothing: nothing needs the whole frame
+    if (blockIdx.x == 0 && tid == 0) { ctrl->n_moves = 0; ctrl->gid_next += (uint32_t)g.M; }
+    return;
+  }
+  // Publish this workgroup's scores and count its arrival.  The scores were written through to
+  // device-coherent memory, so every wave only waits for its own stores to be acknowledged; the
+  // arrival counter is a relaxed device-scope atomic, and the one workgroup that arrives last
+  // invalidates its caches (acquire) before it reads what the others wrote.
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (tid == 0) {
+    const uint32_t prev = __hip_atomic_fetch_add(&ctrl->arrive, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const bool last = prev == gridDim.x - 1;
+    if (last) {
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+      __hip_atomic_store(&ctrl->arrive, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      OVGGT_TRACE_ONLY(ctrl->pad[0] = (uint32_t)wall_clock64();)
+    }
+    sh.is_last = last ? 1u : 0u;
+  }
+  __syncthreads();
+  if (!sh.is_last) return;
+
+  // ---- phase 2: this workgroup saw every other one arrive
+  if (tid == 0) ctrl->gid_next += (uint32_t)g.M;       // once per layer and frame: the next frame's first token id
+  uint32_t* mvdst = (uint32_t*)(mb + g.off_mvdst);
+  uint32_t* mvsrc = (uint32_t*)(mb + g.off_mvsrc);
+  if (smoothing) {
+    smooth_new_scores(sm, g.M, ss + n_old, (float*)mvdst);     // the move list is not written yet: scratch
+    if (n_total <= g.B) {
+      if (tid == 0) ctrl->n_moves = 0;
+      return;
+    }
+  }
+  if (hy.on) hybrid_new_values(sh, hy, smoothing, ss, flags, n_old, n_total);
+  // hybrid scoring keeps the evict bitmap: the centroid's maintenance reads it
+  uint32_t* evbits = hy.on ? (uint32_t*)(mb + g.off_evbits) : nullptr;
+  select_hist(sh, g, ss, ids, flags, ctrl, mvdst, mvsrc, (uint32_t*)(mb + g.off_mvmap), evbits, ghist, n_total);
+}
+
+hipError_t launch_score_select_wide(const Geom& g, const SmoothParams& sm, const HybridParams& hy, char* meta, int layer0, int nl,
+                                    const void* resid, const uint8_t* anchors, int n_total, int n_cus, hipStream_t s) {
+  int cp = 1;
+  while (cp < g.C) cp *= 2;
+  const int e = cp >= 64 ? cp / 64 : 1;
+  int gx = (g.M + kSelWaves - 1) / kSelWaves;
+  if ((long)gx * nl > n_cus) gx = n_cus / nl > 0 ? n_cus / nl : 1;
+  const dim3 grid((unsigned)gx, (unsigned)nl);
+  if (g.esize == 2)
+    hipLaunchKernelGGL(score_select_wide_kernel<true>, grid, dim3(kSelThreads), 0, s, g, sm, hy, meta, layer0, (const char*)resid, anchors, n_total, e);
+  else
+    hipLaunchKernelGGL(score_select_wide_kernel<false>, grid, dim3(kSelThreads), 0, s, g, sm, hy, meta, layer0, (const char*)resid, anchors, n_total, e);
+  return hipGetLastError();
+}
+
+}  // namespace ovggt

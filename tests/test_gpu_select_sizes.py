@@ -1,0 +1,26 @@
+"""The selection's two kernels at the sizes where one takes over from the other or a loop gains a round, against the
+oracle bit for bit: 16 rows are scored without workers, 2048 tokens and 34 chunks of 1024 slots are what one CU holds."""
+import pytest
+
+from paper_2603_05959_amd import synth
+from test_gpu_parity import run_stream
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("M,budget,C,dtype,frames,mode", [
+    (16, 33, 64, "bf16", 8, "stored"), (17, 40, 64, "bf16", 8, "stored"), (16, 50, 1030, "f32", 8, "stored"),
+    (3, 5000, 2052, "bf16", 3, "stored"),
+    (40, 100, 4096, "bf16", 6, "hybrid"), (40, 100, 1025, "bf16", 6, "hybrid"),
+    (1024, 2048, 64, "bf16", 6, "stored"), (1025, 3000, 64, "bf16", 6, "hybrid"), (1029, 3100, 64, "bf16", 6, "both"),
+    (2048, 32768, 64, "bf16", 19, "stored"), (2048, 32769, 64, "bf16", 19, "hybrid"),      # 34 chunks, and a slot more
+    (2048, 4100, 64, "f32", 5, "smooth"), (2049, 4100, 64, "bf16", 5, "both"),
+])
+def test_selection_at_the_edges_of_its_kernels(M, budget, C, dtype, frames, mode):
+    smooth = None
+    ns = 2
+    if mode in ("smooth", "both"):
+        ns = M % 8 or 8
+        smooth = (0.5, 8, (M - ns) // 8, ns, synth.gaussian_kernel3(1.0))
+    cfg = synth.preset(1, M=M, H=1, C=C, B=budget, T=frames, n_special=ns, dtype=dtype)
+    run_stream(cfg, attn_frames=set(), cache_every=3, smooth=smooth, hybrid_beta=0.5 if mode in ("hybrid", "both") else None)
