@@ -1,23 +1,25 @@
 // fp32 attention of the new frame's queries over the resident cache (paper
 // Sec. 3.1), for handles whose dtype is f32.
 //
-// Everything stays in fp32: both products run on v_mfma_f32_16x16x4_f32, the
-// softmax between them on the VALU.
 //   S^T = K Q^T      A = K rows, B = Q^T; a lane holds one query's scores
 //   O^T = V^T P^T    A = V^T, B = P^T straight from the S^T accumulators
 // The order in which a contraction index is walked is free, so operands are
-// taken from memory the way they lie there: of a 16-slot tile lane (l16, g)
-// reads 16-byte pieces of K row l16 (elements 16 j + 4 g .. +3) and of V rows
-// 4 g .. 4 g + 3 (elements 4 l16 .. +3), whole 64- and 256-byte runs, and both
-// enter the matrix unit from these registers; no operand passes through LDS.
+// taken from memory the way they lie there, whole 64- and 256-byte runs, and
+// enter the matrix unit from registers; no operand passes through LDS.
 //
-// 1041 queries over 5137 slots, 16 heads (22 GFLOP): 39.5 ms as a scalar kernel with
-// one workgroup per query, 230 us like this (a step of 253 us less 23 of append and
-// selection; 254 under a trace), 95 TFLOP/s; the f32 matrix rate (157 at 2.4 GHz)
-// bounds it: the matrix pipes are busy 60 % of the time, and what they wait for is K
-// and V out of L2 (11 TB/s: a 16-query block re-reads both).  Blocks of 32 queries
-// halve that traffic but fill the chip worse (528 instead of 1056 blocks for 256 CUs)
-// and took 10 to 20 % longer over every size from 17 to 1041 queries.
+// Two kernels.  The small one works in fp32 throughout, on v_mfma_f32_16x16x4_f32 (157 TFLOP/s at 2.4 GHz): of a 16-slot
+// tile lane (l16, g) reads 16-byte pieces of K row l16 (elements 16 j + 4 g .. +3) and of V rows 4 g .. 4 g + 3 (elements
+// 4 l16 .. +3).
+//
+// The wide one takes every factor as the exact sum of three bf16 numbers and multiplies on v_mfma_f32_16x16x32_bf16, which
+// has 16 times the rate: of the nine products of parts, the six that matter next to 2^-24, accumulated in fp32, small ones
+// first; softmax and sums stay fp32.  A longer contraction per instruction and one rounding of O a tile leave it closer
+// to 64 bits than the fp32 unit does: 1.8e-7 against 2.9e-7 on 1041 queries of 16 heads over 5137 slots, 1.7e-7 against 2.7e-7 on 520 over
+// 2568, 1.6e-7 against 2.6e-7 on 272 over 1572.  Forming the parts is what bounds it (430 of a 32 x 32 tile's vector
+// instructions, beside 96 matrix instructions of 16 cycles); a 32-query block halves that for K and V.  What is left of a value
+// after a part is one v_dot2_f32_bf16 instead of a shift or mask and a subtraction.
+// 1041 queries of 16 heads over 5137 slots (22 GFLOP), attention: 39.5 ms as a scalar kernel, 249 us by the small kernel, 188 (a
+// step of 179 without events around it; before 254) by the wide one.
 #include "attn_parts.h"
 #include <type_traits>
 
@@ -28,12 +30,14 @@ constexpr int kF32Unit = 4;             // exponents of a wave that starts over,
 constexpr float kF32Low = 6.0f;         // how far, in these, its reference lies above the maximum
 constexpr float kF32Far = 0x1p100f;     // weighted sums up to here stay finite when 8 waves of 16 ranges are merged
 constexpr float kF32High = 0x1p24f;     // exponents of the first walk are within 1 of the true ones up to here
-constexpr int kF32Rows = kPartRows;     // queries of a workgroup
+constexpr float kF32Whole = 0x1p-92f;   // values from here on lose nothing in three bf16 parts, nor do sums of their products
+constexpr float kF32Scaled = 0x1p94f;   // query times scale up to which what small keys lose does not count in an exponent
+constexpr int kWideGroups = 2;          // 16-query groups of a workgroup on bf16 parts
 constexpr int kF32MaxRecs = 4096;       // parts of a split launch (17 MB of workspace at most)
 
 // Workspace of an fp32 handle: one record per part.
 size_t attn_f32_ws_bytes(int layer_heads, int tokens_per_frame) {
-  const long blocks = (long)((tokens_per_frame + kF32Rows - 1) / kF32Rows) * layer_heads;
+  const long blocks = (long)((tokens_per_frame + kPartRows - 1) / kPartRows) * layer_heads;
   const long recs = blocks * kMaxSplits < kF32MaxRecs ? blocks * kMaxSplits : kF32MaxRecs;
   return (size_t)recs * part_rec_floats(1) * sizeof(float);
 }
@@ -44,26 +48,41 @@ struct AttnF32Params {
   const float* q;
   float* out;
   float* recs;
-  int layer0, n_total, QB, n_work, splits;
+  int layer0, n_total, QB;
+  int blocks, whole, splits;  // blocks of queries, those that one workgroup has to itself, and the ranges of the others
   float c, c_unit;            // softmax scale * log2(e), and the same over kF32Unit
 };
+
+// Which block of queries and which range of the slots a workgroup takes: every XCD first its share of the whole blocks,
+// then of the ranges of the others, consecutive workgroups along the blocks of one head and range, whose K and V
+// rows then come from that XCD's L2.
+struct F32Place { int block, range, ranges; };
+__device__ inline bool f32_place(const AttnF32Params& p, F32Place* at) {
+  const unsigned wg = blockIdx.y * gridDim.x + blockIdx.x, xcd = wg & 7, i = wg >> 3;
+  const unsigned whole_x = (unsigned)p.whole >> 3;                     // a multiple of 8
+  if (i < whole_x) {
+    *at = {(int)(xcd * whole_x + i), 0, 1};
+    return true;
+  }
+  const unsigned rest = (unsigned)(p.blocks - p.whole), parts = rest * (unsigned)p.splits;
+  const unsigned j = xcd * ((parts + 7) >> 3) + (i - whole_x);
+  if (i - whole_x >= ((parts + 7) >> 3) || j >= parts) return false;
+  *at = {p.whole + (int)(j % rest), (int)(j / rest), p.splits};
+  return true;
+}
 
 // A workgroup takes 16 queries of one head over one of `splits` equal ranges of
 // the slots; its waves share the 16-slot tiles of the range (wave w: every 8th
 // from the w-th) and merge through LDS.  With more than one range, the parts go
 // to memory and the workgroup that arrives last for a query block merges them.
 __global__ void __launch_bounds__(kPartThreads)
-attn_f32_kernel(Geom g, AttnF32Params p) {
+attn_f32_small_kernel(Geom g, AttnF32Params p) {
   constexpr int W = kPartWaves;
   __shared__ MergeArea<1> area;
-  // Consecutive workgroups of an XCD walk the query blocks of one range of one head, whose K and V
-  // rows then come from that XCD's L2.
-  const unsigned wg = blockIdx.y * gridDim.x + blockIdx.x;
-  const int idx = (int)((wg & 7) * (gridDim.x >> 3) * gridDim.y + (wg >> 3));
-  if (idx >= p.n_work) return;                                       // whole workgroup
-  const int qb = idx % p.QB, rest = idx / p.QB;
-  const int sp = rest % p.splits, lh = rest / p.splits;
-  const int q0 = qb * kF32Rows;
+  F32Place at;
+  if (!f32_place(p, &at)) return;                                    // whole workgroup
+  const int qb = at.block % p.QB, lh = at.block / p.QB, sp = at.range, splits = at.ranges;
+  const int q0 = qb * kPartRows;
   const int li = lh / g.H, h = lh - li * g.H;
   const int lane = threadIdx.x & 63, l16 = lane & 15, gl = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -77,7 +96,7 @@ attn_f32_kernel(Geom g, AttnF32Params p) {
     for (int j = 0; j < 4; ++j) qf[j] = *(const f32x4*)(qp + 16 * j);
   }
   const int n_total = p.n_total, nt = (n_total + 15) >> 4;
-  const int t0 = (int)((long)nt * sp / p.splits), t1 = (int)((long)nt * (sp + 1) / p.splits);
+  const int t0 = (int)((long)nt * sp / splits), t1 = (int)((long)nt * (sp + 1) / splits);
   const bool ragged = (n_total & 15) != 0;
   if (nt == 1 && wave > 0) return;                                   // one tile: one wave has it all
   f32x4 O[1][4];
@@ -174,18 +193,294 @@ attn_f32_kernel(Geom g, AttnF32Params p) {
     return;
   }
   uint32_t* arrive = (uint32_t*)(layer_meta(p.meta, g, p.layer0 + li) + g.off_arrive) + (size_t)h * p.QB + qb;
-  const size_t first = (size_t)lh * p.splits * p.QB + qb;              // record of range 0; the ranges are QB apart
-  merge_and_write<kF32Unit>(area, O, m, l, sp, p.splits, arrive, p.recs + first * part_rec_floats(1), (size_t)p.QB * part_rec_floats(1),
+  const int rest = p.blocks - p.whole;                   // records: the ranges of a block are `rest` apart
+  merge_and_write<kF32Unit>(area, O, m, l, sp, splits, arrive, p.recs + (size_t)(at.block - p.whole) * part_rec_floats(1), (size_t)rest * part_rec_floats(1),
                      [&](int row, int piece, const f32x4& r) {
                        if (q0 + row < g.M) *(f32x4*)(p.out + (((size_t)li * g.M + q0 + row) * g.H + h) * 64 + 4 * piece) = r;
                      });
 }
 
-// Ranges per query block.  Fewer blocks than CUs: one range more for every CU that would idle, as long
+typedef __attribute__((ext_vector_type(2))) float f32x2;
+typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+
+// Eight fp32 values as three bf16 each, x = part[0] + part[1] + part[2]: rounded to nearest, what is left, and what is
+// left of that.  Three significands of 8 bits hold one of 24, so nothing is lost unless a part falls below bf16's
+// smallest number (x < 2^-100) or rounds up past its largest (then a part is infinite or NaN).
+struct Parts { u32x4 part[3]; };
+__device__ inline Parts in_parts(const float (&x)[8]) {
+  Parts r;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    float a = x[2 * e], b = x[2 * e + 1];
+    uint32_t fw = 0x0000BF80u, sw = 0xBF800000u;       // (-1, 0) and (0, -1)
+    asm("" : "+v"(fw), "+v"(sw));
+    const bf16x2 first = __builtin_bit_cast(bf16x2, fw), second = __builtin_bit_cast(bf16x2, sw);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      const bf16x2 w = __builtin_convertvector((f32x2{a, b}), bf16x2);
+      r.part[i][e] = __builtin_bit_cast(uint32_t, w);
+      if (i < 2) {
+        a = __builtin_amdgcn_fdot2_f32_bf16(w, first, a, false);
+        b = __builtin_amdgcn_fdot2_f32_bf16(w, second, b, false);
+      }
+    }
+  }
+  return r;
+}
+__device__ inline f32x4 mul_parts(const u32x4& a, const u32x4& b, const f32x4& c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+// The products that matter next to 2^-24 of the largest, smallest first.
+__device__ inline f32x4 mul_small(const Parts& a, const Parts& b, f32x4 c) {
+  c = mul_parts(a.part[2], b.part[0], c);
+  c = mul_parts(a.part[0], b.part[2], c);
+  c = mul_parts(a.part[1], b.part[1], c);
+  c = mul_parts(a.part[1], b.part[0], c);
+  return mul_parts(a.part[0], b.part[1], c);
+}
+
+// The tiles of one wave (t, t + 8, ... below t1) once more, both products in fp32.
+// Scores times c leave the fp32 range where scores times the scale do not, and above 2^24 what a fused exponent
+// leaves of the largest score's rounding is no longer small: exponents in units of 2^4, rounded before the reference
+// is taken off, count every score that is finite once scaled.
+// Sums of weights up to 2^8, or of many weights of 1 that turn out to be small beside another wave's, leave the fp32
+// range where values of V are near its end, although the result, a mean of them, does not: with weights up to
+// 2^-24 (low = 6 units), 2^17 slots of any value stay below the largest number.  Small values keep weights up to 1 (low = 0).
+__device__ __forceinline__ void second_walk(const float* qp, const float* kbase, const float* vbase, int n_total, int t, int t1,
+                                                      float c, float low, f32x4 (&O)[4], float& m, float& l) {
+  const int lane = threadIdx.x & 63, l16 = lane & 15, gl = lane >> 4;
+  m = -3.402823466e38f;
+  l = 0.f;
+#pragma unroll
+  for (int d = 0; d < 4; ++d) O[d] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (; t < t1; t += kPartWaves)
+#pragma unroll 1
+    for (int s0 = t * 32; s0 < min(t * 32 + 32, n_total); s0 += 16) {
+      f32x4 S = {0.f, 0.f, 0.f, 0.f}, vf[4];
+      const float* kp = kbase + (size_t)min(s0 + l16, n_total - 1) * 64 + 4 * gl;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const f32x4 kf = *(const f32x4*)(kp + 16 * j), qf = *(const f32x4*)(qp + 4 * gl + 16 * j);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) S = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[e], qf[e], S, 0, 0, 0);
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const bool absent = s0 + 4 * gl + i >= n_total;
+        vf[i] = *(const f32x4*)(vbase + (size_t)min(s0 + 4 * gl + i, n_total - 1) * 64 + 4 * l16);
+        S[i] = absent ? -INFINITY : S[i];
+        if (absent) vf[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+      }
+      const float mx = fmaxf(fmaxf(S[0], S[1]), fmaxf(S[2], S[3])) * c;
+      if (__builtin_amdgcn_ballot_w64(mx > m - low) != 0ull) {
+        float x = fmaxf(mx, __shfl_xor(mx, 16, 64));
+        x = fmaxf(x, __shfl_xor(x, 32, 64));
+        const float mn = fmaxf(m, x + low), a = __builtin_amdgcn_exp2f(kF32Unit * (m - mn));
+        m = mn;
+        l *= a;
+#pragma unroll
+        for (int d = 0; d < 4; ++d) O[d] *= a;
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) S[i] = __builtin_amdgcn_exp2f(kF32Unit * (S[i] * c - m));
+      l += (S[0] + S[1]) + (S[2] + S[3]);
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int d = 0; d < 4; ++d) O[d] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[i][d], S[i], O[d], 0, 0, 0);
+    }
+}
+
+// A workgroup takes G groups of 16 queries of one head over one of `splits` equal ranges of
+// the slots; its waves share the 32-slot tiles of the range (wave w: every 8th
+// from the w-th) and merge through LDS.  With more than one range, the parts go
+// to memory and the workgroup that arrives last for a query block merges them.
+template <int G>
+__global__ void __launch_bounds__(kPartThreads)
+attn_f32_wide_kernel(Geom g, AttnF32Params p) {
+  constexpr int W = kPartWaves;
+  __shared__ MergeArea<G> area;
+  F32Place at;
+  if (!f32_place(p, &at)) return;                                    // whole workgroup
+  const int qb = at.block % p.QB, lh = at.block / p.QB, sp = at.range, splits = at.ranges;
+  const int q0 = qb * G * kPartRows;
+  const int li = lh / g.H, h = lh - li * g.H;
+  const int lane = threadIdx.x & 63, l16 = lane & 15, gl = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const float* kbase = (const float*)layer_k((char*)p.kv, g, p.layer0 + li) + (size_t)h * g.cap * 64;
+  const float* vbase = (const float*)layer_v((char*)p.kv, g, p.layer0 + li) + (size_t)h * g.cap * 64;
+  auto query = [&](int q) { return p.q + (((size_t)li * g.M + min(q0 + q * kPartRows + l16, g.M - 1)) * g.H + h) * 64; };
+
+  const int n_total = p.n_total, nt = (n_total + 31) >> 5;
+  const int t0 = (int)((long)nt * sp / splits), t1 = (int)((long)nt * (sp + 1) / splits);
+  if (nt == 1 && wave > 0) return;                                   // one tile: one wave has it all
+  const float c = p.c;
+  f32x4 kf[2][4], vf[2][4];
+  // Of a 32-slot tile a lane reads rows l16 and 16 + l16 of K (elements 32 j + 8 gl .. +7) and rows 4 gl + i and
+  // 16 + 4 gl + i of V (elements 4 l16 .. +3).  Rows at or beyond n_total are never read (they may hold anything): the
+  // last resident row stands in.
+  auto load_k = [&](int t) {
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      const float* kp = kbase + (size_t)min(t * 32 + 16 * b + l16, n_total - 1) * 64 + 8 * gl;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) kf[b][j] = *(const f32x4*)(kp + 32 * (j >> 1) + 4 * (j & 1));
+    }
+  };
+  auto load_v = [&](int t) {
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        vf[b][i] = *(const f32x4*)(vbase + (size_t)min(t * 32 + 16 * b + 4 * gl + i, n_total - 1) * 64 + 4 * l16);
+  };
+  if (t0 + wave < t1) { load_k(t0 + wave); load_v(t0 + wave); }
+  Parts qf[G][2];
+  bool far[G];                  // the first walk does not hold
+#pragma unroll
+  for (int q = 0; q < G; ++q) {
+    float most = 0.f, least = INFINITY;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const f32x4 a = *(const f32x4*)(query(q) + 32 * j + 8 * gl), b = *(const f32x4*)(query(q) + 32 * j + 8 * gl + 4);
+      const float x[8] = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
+      qf[q][j] = in_parts(x);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        most = fmaxf(most, fabsf(x[e]));
+        least = fminf(least, x[e] == 0.f ? INFINITY : fabsf(x[e]));
+      }
+    }
+    far[q] = !(most * c <= kF32Scaled) || !(least >= kF32Whole);
+  }
+  const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+  f32x4 O[G][4];
+  float m[G], l[G];
+#pragma unroll
+  for (int q = 0; q < G; ++q) {
+    m[q] = -3.402823466e38f;
+    l[q] = 0.f;
+#pragma unroll
+    for (int d = 0; d < 4; ++d) O[q][d] = zero;
+  }
+  for (int t = t0 + wave; t < t1; t += W) {
+    const int tn = min(t + W, t1 - 1);
+    f32x4 S[G][2];
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      f32x4 low[G];
+#pragma unroll
+      for (int q = 0; q < G; ++q) low[q] = S[q][b] = zero;
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const float x[8] = {kf[b][2 * j][0], kf[b][2 * j][1], kf[b][2 * j][2], kf[b][2 * j][3],
+                            kf[b][2 * j + 1][0], kf[b][2 * j + 1][1], kf[b][2 * j + 1][2], kf[b][2 * j + 1][3]};
+        const Parts k = in_parts(x);
+#pragma unroll
+        for (int q = 0; q < G; ++q) {
+          low[q] = mul_small(k, qf[q][j], low[q]);
+          S[q][b] = mul_parts(k.part[0], qf[q][j].part[0], S[q][b]);
+        }
+      }
+#pragma unroll
+      for (int q = 0; q < G; ++q) S[q][b] += low[q];
+    }
+    load_k(tn);                                          // K of the next tile travels during this tile's P V, V during its Q K
+    if (t * 32 + 32 > n_total) {                         // absent slots: no weight, and no 0 * inf from the stand-in row
+      asm volatile("");                                  // a branch: as selects they would be done for every tile
+#pragma unroll
+      for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const bool absent = t * 32 + 16 * b + 4 * gl + i >= n_total;
+#pragma unroll
+          for (int q = 0; q < G; ++q) S[q][b][i] = absent ? -INFINITY : S[q][b][i];
+          if (absent) vf[b][i] = zero;
+        }
+    }
+    Parts P[G];
+#pragma unroll
+    for (int q = 0; q < G; ++q) {
+      // The reference m follows the maximum only when it is passed by 2^8 (weights are fp32: no
+      // accuracy is lost), so most tiles rescale nothing and look at no other lane.
+      const float mx = fmaxf(fmaxf(fmaxf(S[q][0][0], S[q][0][1]), fmaxf(S[q][0][2], S[q][0][3])),
+                             fmaxf(fmaxf(S[q][1][0], S[q][1][1]), fmaxf(S[q][1][2], S[q][1][3]))) * c;
+      if (__builtin_amdgcn_ballot_w64(mx > m[q] + kF32Lag) != 0ull) {
+        float x = fmaxf(mx, __shfl_xor(mx, 16, 64));
+        x = fmaxf(x, __shfl_xor(x, 32, 64));
+        const float mn = fmaxf(m[q], x), a = __builtin_amdgcn_exp2f(m[q] - mn);
+        m[q] = mn;
+        l[q] *= a;
+#pragma unroll
+        for (int d = 0; d < 4; ++d) O[q][d] *= a;
+      }
+      float w[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) w[e] = __builtin_amdgcn_exp2f(fmaf(S[q][e >> 2][e & 3], c, -m[q]));
+      l[q] += ((w[0] + w[1]) + (w[2] + w[3])) + ((w[4] + w[5]) + (w[6] + w[7]));
+      P[q] = in_parts(w);
+    }
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+      const float x[8] = {vf[0][0][d], vf[0][1][d], vf[0][2][d], vf[0][3][d], vf[1][0][d], vf[1][1][d], vf[1][2][d], vf[1][3][d]};
+      const Parts v = in_parts(x);
+#pragma unroll
+      for (int q = 0; q < G; ++q) O[q][d] += mul_parts(v.part[0], P[q].part[0], mul_small(v, P[q], zero));     // one rounding of O a tile
+    }
+    load_v(tn);
+  }
+  // Where the first walk does not hold, the wave starts over on the fp32 matrix unit, in the units that serve the whole
+  // range: parts too small for bf16 (of a query, of keys next to a large scale, of values, whose weighted sums then are
+  // small or nothing), parts beyond its largest number (infinities and NaN stay in the sums), and what an fp32
+  // softmax with a fused exponent leaves out: see the second walk.
+#pragma unroll
+  for (int q = 0; q < G; ++q) {
+    float size = 0.f, least = INFINITY;
+#pragma unroll
+    for (int d = 0; d < 4; ++d)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        size += fabsf(O[q][d][i]);
+        least = fminf(least, fabsf(O[q][d][i]));
+      }
+    const bool large = !(size <= kF32Far) || !(fabsf(m[q]) <= kF32High);          // a wave without tiles, too: its m stays the lowest
+    if (__builtin_amdgcn_ballot_w64(far[q] || large || !(least >= kF32Whole)) != 0ull)
+      second_walk(query(q), kbase, vbase, n_total, t0 + wave, t1, p.c_unit, __builtin_amdgcn_ballot_w64(large) != 0ull ? kF32Low : 0.f, O[q], m[q], l[q]);
+    else m[q] *= 1.0f / kF32Unit;
+  }
+
+#pragma unroll
+  for (int q = 0; q < G; ++q) {
+    l[q] += __shfl_xor(l[q], 16, 64);
+    l[q] += __shfl_xor(l[q], 32, 64);
+  }
+  if (nt == 1) {                                         // nothing to merge: 2 queries over 10 slots of 1536 heads 13.8 -> 7.9 us
+#pragma unroll
+    for (int q = 0; q < G; ++q) {
+      const int row = q0 + q * kPartRows + l16;
+      if (row < g.M) {
+        float* o = p.out + (((size_t)li * g.M + row) * g.H + h) * 64 + 16 * gl;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) *(f32x4*)(o + 4 * i) = f32x4{O[q][0][i] / l[q], O[q][1][i] / l[q], O[q][2][i] / l[q], O[q][3][i] / l[q]};
+      }
+    }
+    return;
+  }
+  uint32_t* arrive = (uint32_t*)(layer_meta(p.meta, g, p.layer0 + li) + g.off_arrive) + (size_t)h * p.QB + qb;
+  const int rest = p.blocks - p.whole;                   // records: the ranges of a block are `rest` apart
+  merge_and_write<kF32Unit>(area, O, m, l, sp, splits, arrive, p.recs + (size_t)(at.block - p.whole) * part_rec_floats(G), (size_t)rest * part_rec_floats(G),
+                     [&](int row, int piece, const f32x4& r) {
+                       if (q0 + row < g.M) *(f32x4*)(p.out + (((size_t)li * g.M + q0 + row) * g.H + h) * 64 + 4 * piece) = r;
+                     });
+}
+
+// Ranges per query block of the small kernel.  Fewer blocks than CUs: one range more for every CU that would idle, as long
 // as a range keeps 16 tiles, two for each wave (step time, 65 queries of 2 heads over 4161 slots: 60 us
 // with 1 range, 33 with 4, 29 with 16; 700 queries of one head over 4796: 68 with 1, 36 with 4, 41 with 6;
 // 17 of 8 heads over 1017: 28 with 1, 24 with 4).  More blocks than CUs: ranges smooth the last,
-// partly filled round (1056 blocks = 4.1 a CU: 286 us with 1 range, 259 with 2, 250 with 3 and with 16).
+// partly filled round.
 static int f32_splits(long blocks, int n_tiles, long max_recs, long cus) {
   long s = 1;
   if (blocks < cus) {
@@ -204,12 +499,38 @@ static int f32_splits(long blocks, int n_tiles, long max_recs, long cus) {
   return s < 1 ? 1 : (int)s;
 }
 
+// The other kernel's launches: whole rounds of blocks to one workgroup each, as many as fill the device, and what is left
+// over in ranges of the slots (attention of 1041 queries of 16 heads over 5137 slots, 2.06 rounds: 188 us, with every block
+// in three or four ranges 230).  In tiles of 16 slots for each of 8 waves: a workgroup takes about 4 besides its own.
+static void f32_rounds(long blocks, int n_tiles, long max_recs, long cus, long* whole, int* splits) {
+  *whole = blocks / cus * cus;
+  *splits = 1;
+  const long rest = blocks - *whole;
+  float best = INFINITY;
+  for (long s = 1; rest > 0 && s <= kMaxSplits && (s == 1 || (s <= n_tiles / 16 && rest * s <= max_recs)); ++s) {
+    const float t = (float)((rest * s + cus - 1) / cus) * ((float)n_tiles / (float)(kPartWaves * s) + 4.f);
+    if (t < 0.97f * best) { best = t; *splits = (int)s; }
+  }
+}
+
+// Blocks of 32 queries on three bf16 parts where blocks of 16 would fill the device more than once: attention of 1041
+// queries of 16 heads over 5137 slots 249 us there, 188 here; 272 over 1572 38 and 31; fewer take longer here (300 queries of 6
+// heads over 1500 slots 16 and 19: each workgroup's first tile and merge, 17 KB of code to fetch).  Up to eight times, which
+// covers a layer of any frame; batched layers and longer sequences keep the small kernel, whose sums over more ranges are shorter.
+static bool f32_wide(const Geom& g, int nl, int n_wgs) {
+  const long blocks = (long)((g.M + kPartRows - 1) / kPartRows) * g.H * nl;
+  return blocks > n_wgs && blocks <= 8L * n_wgs && (long)g.H * ((g.M + kWideGroups * kPartRows - 1) / (kWideGroups * kPartRows)) <= kMaxArrive;
+}
+
 AttnSplit attn_f32_split(const Geom& g, int nl, int n_total, size_t ws_bytes, int n_wgs) {
   AttnSplit sp;
-  sp.rows = kF32Rows;
-  const long blocks = (long)((g.M + kF32Rows - 1) / kF32Rows) * g.H * nl;
-  sp.ranges = f32_splits(blocks, (n_total + 15) / 16, (long)(ws_bytes / (part_rec_floats(1) * sizeof(float))), n_wgs);
-  sp.work = blocks * sp.ranges;
+  const int G = f32_wide(g, nl, n_wgs) ? kWideGroups : 1, n_tiles = (n_total + 15) / 16;
+  const long max_recs = (long)(ws_bytes / (part_rec_floats(G) * sizeof(float)));
+  sp.rows = G * kPartRows;
+  sp.blocks = (long)((g.M + sp.rows - 1) / sp.rows) * g.H * nl;
+  if (G > 1) f32_rounds(sp.blocks, n_tiles, max_recs, n_wgs, &sp.whole, &sp.ranges);
+  else sp.ranges = f32_splits(sp.blocks, n_tiles, max_recs, n_wgs);
+  sp.work = sp.whole + (sp.blocks - sp.whole) * sp.ranges;
   return sp;
 }
 
@@ -229,14 +550,15 @@ hipError_t launch_attn_f32(const Geom& g, char* kv, char* meta, int layer0, int 
   p.kv = kv; p.meta = meta; p.q = (const float*)q; p.out = (float*)out;
   p.recs = (float*)ws;
   p.layer0 = layer0; p.n_total = n_total;
-  p.QB = (g.M + kF32Rows - 1) / kF32Rows;
+  p.QB = (g.M + sp.rows - 1) / sp.rows;
   p.c = scale * 1.4426950408889634f;
   p.c_unit = (scale / kF32Unit) * 1.4426950408889634f;
-  p.splits = sp.ranges;
+  if (sp.blocks > 0x7FFFFFFFL) return hipErrorInvalidValue;
+  p.blocks = (int)sp.blocks; p.whole = (int)sp.whole; p.splits = sp.ranges;
   unsigned gx, gy;
   if (!attn_f32_grid(sp.work, &gx, &gy)) return hipErrorInvalidValue;
-  p.n_work = (int)sp.work;
-  hipLaunchKernelGGL(attn_f32_kernel, dim3(gx, gy), dim3(kPartThreads), 0, s, g, p);
+  if (sp.rows == kPartRows) hipLaunchKernelGGL(attn_f32_small_kernel, dim3(gx, gy), dim3(kPartThreads), 0, s, g, p);
+  else hipLaunchKernelGGL(attn_f32_wide_kernel<kWideGroups>, dim3(gx, gy), dim3(kPartThreads), 0, s, g, p);
   return hipGetLastError();
 }
 

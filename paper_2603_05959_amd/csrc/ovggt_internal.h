@@ -87,7 +87,8 @@ hipError_t launch_append(const Geom& g, char* kv, char* meta, int layer0, int nl
 // per compute unit (a multiple of 8, at most kMaxAttnWgs); every rule on how to cut a launch asks for it.
 struct AttnSplit {
   int rows, ranges;          // queries of a workgroup; ranges of the slots, a workgroup for each
-  long work;                 // blocks of queries x ranges
+  long work;                 // workgroups
+  long blocks = 0, whole = 0;   // blocks of queries; fp32: those of them that are not cut into ranges
 };
 AttnSplit attn_f32_split(const Geom& g, int nl, int n_total, size_t ws_bytes, int n_wgs);
 bool attn_f32_grid(long work, unsigned* x, unsigned* y);

@@ -1,0 +1,65 @@
+"""The fp32 attention on bf16 parts (launches with more blocks of 16 queries than the device has compute units) against fp64
+softmax: edges of its 32-query blocks and 32-slot tiles, whole blocks beside ranges, and values that bf16 parts do not hold."""
+import numpy as np
+import pytest
+
+from paper_2603_05959_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+
+
+def _run(M, n_old, H, layers=1, change=None, scale=0.0):
+    import torch
+    gen = torch.Generator().manual_seed(M * 1000 + n_old)
+    n_old = max(n_old, M)
+    cache = B.Cache(layers, H, 64, M, 64, n_old, "f32", softmax_scale=scale)
+    route = B.ovggt_attn_route(cache.cfg, layers, n_old + M)
+    assert route["rows"] == 32, route
+    q, k, v = (torch.randn(layers, n, H, 64, generator=gen) for n in (M, n_old + M, n_old + M))
+    if change:
+        change(q, k, v)
+    for l in range(layers):
+        cache.import_(l, 3 + n_old // M, np.arange(n_old, dtype=np.uint32), k[l, :n_old].numpy(), v[l, :n_old].numpy(),
+                      np.ones(n_old, np.float32), np.zeros(n_old, np.uint8))
+    out = cache.new_output()
+    cache.step(q.cuda(), k[:, n_old:].contiguous().cuda(), v[:, n_old:].contiguous().cuda(), torch.ones(layers, M, 64, device="cuda"), None, out)
+    got = out.cpu().double()
+    cache.close()
+    p = torch.softmax(torch.einsum("lmhd,lnhd->lhmn", q.double(), k.double()) * (float(np.float32(scale)) or 0.125), dim=-1)
+    return got, torch.einsum("lhmn,lnhd->lmhd", p, v.double()), route
+
+
+@pytest.mark.parametrize("M,n_old,H,layers", [
+    (1, 1, 300, 1), (1, 30, 300, 1), (1, 31, 300, 1), (1, 32, 300, 1),        # one tile, ragged and full; one slot of the next
+    (16, 240, 260, 1), (17, 239, 130, 1), (31, 300, 130, 1), (32, 224, 130, 1), (33, 300, 100, 1),   # queries of a block; eight tiles
+    (300, 300, 16, 1), (65, 700, 86, 1), (97, 600, 16, 5),                    # the rest of a round in ranges, after whole rounds too
+])
+def test_blocks_and_tiles(M, n_old, H, layers):
+    got, ref, _ = _run(M, n_old, H, layers)
+    # as in the other kernel's test, without its scaled rows: scores up to about 6
+    assert (got - ref).norm() / ref.norm() < 1e-6
+
+
+def test_range_of_values():
+    import torch
+    M, n_old, H = 300, 400, 16
+
+    def only(f):
+        return _run(M, n_old, H, change=f)
+    def zero_column(q, k, v): v[..., 5] = 0.0
+    def small_queries(q, k, v): q *= 1e-37
+    def small_values(q, k, v): v *= 1e-37
+    def large_values(q, k, v): v.mul_(1e37).clamp_(-3.3e38, 3.3e38); v[:, 7, :, 3] = 3.4e38       # rounds to infinity in bf16
+    def large_keys(q, k, v): k[:, 9] *= 8.0
+    def minus_infinity(q, k, v): q[..., 2] = q[..., 2].abs() + 0.1; k[:, ::3, :, 2] = -float("inf")
+    for f in (zero_column, small_values, large_values, large_keys, minus_infinity):
+        got, ref, _ = only(f)
+        assert torch.isfinite(got).all(), f.__name__
+        # large keys: scores up to 50 with errors of a few 2^-24 of that; elsewhere as above
+        worst = 5e-6 if f is large_keys else 1e-6
+        assert (got - ref).norm() / ref.norm() < worst, (f.__name__, float((got - ref).norm() / ref.norm()))
+    got, ref, _ = _run(M, n_old, H, change=small_queries, scale=1e37)
+    assert (got - ref).norm() / ref.norm() < 2e-6
+    got, ref, _ = _run(M, n_old, H, change=lambda q, k, v: k.mul_(1e-37), scale=1e37)
+    assert (got - ref).norm() / ref.norm() < 2e-6
+    assert (only(zero_column)[0][..., 5] == 0).all()
