@@ -267,12 +267,18 @@ static int global_attn_impl(ovggt_cache* c, int layer, const void* q, const void
     if (flush_pending(c, l0, nl, s) != OVGGT_OK) return OVGGT_ERR_HIP;
     all_pending = false;
   }
-  {
+  const bool few = g.esize == 2 && attn_few_better(g, nl, n + g.M, c->n_wgs);
+  if (all_pending && n != g.B) return OVGGT_ERR_HIP;              // a pending compaction implies a full cache
+  // the attention kernel appends where it can, unless every kernel is timed: then the append is a launch of its own (the
+  // same values either way)
+  const int appends = few && !prof_all && attn_few_appends(g, nl, n + g.M, ws_bytes, c->n_wgs) ? (all_pending ? 2 : 1) : 0;
+  if (!appends) {
     ProfScope ps(c, OVGGT_PROF_APPEND, s, prof_all);
     if (launch_append(g, c->kv, c->meta, l0, nl, k_new, v_new, n, all_pending, s) != hipSuccess)
       return OVGGT_ERR_HIP;
   }
-  for (int l = l0; l < l0 + nl; ++l) c->pending[l] = 0;
+  if (!appends)
+    for (int l = l0; l < l0 + nl; ++l) c->pending[l] = 0;
   hipError_t e;
   if (g.esize == 2) {
     hipEvent_t ev[3] = {nullptr, nullptr, nullptr};
@@ -284,11 +290,10 @@ static int global_attn_impl(ovggt_cache* c, int layer, const void* q, const void
         for (hipEvent_t x : ev)
           if (x) c->prof_free.push_back(x);
     }
-    const bool few = attn_few_better(g, nl, n + g.M, c->n_wgs);
     if (few) {                                                    // one kernel, merges included
       e = have ? hipEventRecord(ev[0], s) : hipSuccess;
       if (e == hipSuccess)
-        e = launch_attn_few(g, c->kv, c->meta, l0, nl, q, out, n + g.M, c->scale, ws, ws_bytes, c->n_wgs,
+        e = launch_attn_few(g, c->kv, c->meta, l0, nl, q, k_new, v_new, appends, out, n + g.M, c->scale, ws, ws_bytes, c->n_wgs,
                             c->cfg.out_dtype == OVGGT_F32, s);
       if (have && e == hipSuccess) e = hipEventRecord(ev[1], s);
     } else {
@@ -305,7 +310,7 @@ static int global_attn_impl(ovggt_cache* c, int layer, const void* q, const void
     e = launch_attn_f32(g, c->kv, c->meta, l0, nl, q, out, n + g.M, c->scale, ws, ws_bytes, c->n_wgs, s);
   }
   if (e != hipSuccess) return OVGGT_ERR_HIP;
-  for (int l = l0; l < l0 + nl; ++l) { c->n[l] = n + g.M; c->phase[l] = 1; }
+  for (int l = l0; l < l0 + nl; ++l) { c->n[l] = n + g.M; c->phase[l] = 1; c->pending[l] = 0; }
   return OVGGT_OK;
 }
 

@@ -95,9 +95,13 @@ bool attn_f32_grid(long work, unsigned* x, unsigned* y);
 hipError_t launch_attn_f32(const Geom& g, char* kv, char* meta, int layer0, int nl, const void* q, void* out,
                            int n_total, float scale, char* ws, size_t ws_bytes, int n_wgs, hipStream_t s);
 size_t attn_f32_ws_bytes(int layer_heads, int tokens_per_frame);
-// The same over the half-precision cache of bf16 handles, for launches that attn_few_better names.
-hipError_t launch_attn_few(const Geom& g, char* kv, char* meta, int layer0, int nl, const void* q, void* out,
-                           int n_total, float scale, char* ws, size_t ws_bytes, int n_wgs, bool out_f32, hipStream_t s);
+// The same over the half-precision cache of bf16 handles, for launches that attn_few_better names.  appends: 0, or where
+// attn_few_appends says that every head is one workgroup's, 1: the launch appends the frame's rows itself (as
+// launch_append does), 2: with the outstanding compaction.
+bool attn_few_appends(const Geom& g, int nl, int n_total, size_t ws_bytes, int n_wgs);
+hipError_t launch_attn_few(const Geom& g, char* kv, char* meta, int layer0, int nl, const void* q, const void* k_new, const void* v_new,
+                           int appends, void* out, int n_total, float scale, char* ws, size_t ws_bytes, int n_wgs, bool out_f32,
+                           hipStream_t s);
 bool attn_few_better(const Geom& g, int nl, int n_total, int n_wgs);
 AttnSplit attn_few_split(const Geom& g, int nl, int n_total, size_t ws_bytes, int n_wgs);
 // `ev` (optional, 3 events) are recorded before the main kernel, between it and

@@ -1,0 +1,46 @@
+"""Launches in which every head is one workgroup's: the attention kernel appends the frame's rows, and carries the previous
+frame's moves, itself.  Cache bit for bit against the oracle; one token more, or a longer cache, goes by the append kernel."""
+import numpy as np
+import pytest
+
+from oracle import ovggt_oracle as oc
+from paper_2603_05959_amd import binding as B
+from paper_2603_05959_amd import synth
+from test_gpu_parity import compare_cache, dev, run_stream
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("M,H,budget,hybrid", [
+    (1, 1, 3, False), (1, 16, 188, True), (8, 2, 17, True), (15, 3, 60, False), (16, 2, 200, True), (17, 2, 200, False),
+    (7, 4, 472, False), (7, 4, 474, True),              # 480 resident slots: the last in one range; two ranges
+])
+def test_streams_match_the_oracle(M, H, budget, hybrid):
+    cfg = synth.preset(1, M=M, H=H, C=64, B=budget, T=budget // M + 6, n_special=1 if M > 1 else 0)
+    run_stream(cfg, cache_every=5, attn_frames={0, 1, cfg.T - 2, cfg.T - 1}, hybrid_beta=0.5 if hybrid else None, kernel="few")
+
+
+def test_many_layers_of_up_to_64_tokens_and_values_beyond_half():
+    """192 heads: 64 tokens to a workgroup, so the whole frame of a head."""
+    torch = pytest.importorskip("torch")
+    cfg = synth.preset(1, M=60, H=16, C=64, B=200, T=6, n_special=2, L=12)
+    route = B.ovggt_attn_route(B.make_config(cfg.L, cfg.H, 64, cfg.M, cfg.C, cfg.B, "bf16"), cfg.L, cfg.B + cfg.M)
+    assert route["kernel"] == "few" and route["ranges"] == 1 and route["rows"] == 64, route
+    cache = B.Cache(cfg.L, cfg.H, 64, cfg.M, cfg.C, cfg.B, "bf16")
+    orcs = {l: oc.OracleCache(cfg.M, cfg.H, 64, cfg.B) for l in (0, 11)}
+    out = cache.new_output()
+    for t in range(cfg.T):
+        fs = [synth.frame_inputs(cfg, l if l in orcs else 1, t) for l in range(cfg.L)]
+        if t == cfg.T - 1:
+            fs[11]["v"] = synth.quantise(fs[11]["v"] * 1e5, "bf16")
+        q, k, v, r = (dev(np.stack([f[x] for f in fs]), cfg) for x in "qkvr")
+        cache.step(q, k, v, r, torch.from_numpy(np.stack([f["a"] for f in fs])).cuda(), out)
+        for l, o in orcs.items():
+            o.append(fs[l]["k"], fs[l]["v"])
+            if t < cfg.T - 1:
+                ref = o.attend(fs[l]["q"])
+                assert np.abs(out[l].float().cpu().numpy() - ref).max() < 2e-2 * np.sqrt((ref ** 2).mean()), (t, l)
+            o.update(fs[l]["r"], fs[l]["a"])
+            compare_cache(cache, o, layer=l)
+    assert cache.status(0) == 0 and cache.status(11) == B.OVGGT_STATUS_VRANGE
+    cache.close()
