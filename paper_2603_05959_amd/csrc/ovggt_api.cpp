@@ -28,6 +28,7 @@ struct ovggt_cache {
   std::vector<int8_t> phase;       // 0: expects global_attn, 1: score_select, 2: compact
   std::vector<int8_t> pending;     // 1: the layer's last move list has not been applied yet (n == B); the next
                                    // append applies it, anything else that touches the cache flushes it first
+  std::vector<int32_t> div_parts;  // (min, max) pairs per layer of the frame's diversity pass, where global_attn has done it
   // optional kernel timing (ovggt_profile_*): event pairs per kernel class
   int prof_level = 0, prof_every = 1;
   int64_t prof_calls = 0;
@@ -226,6 +227,7 @@ int ovggt_cache_init(ovggt_cache** out, const ovggt_config* cfg, void* kv_dev, v
   c->frames.assign(c->g.L, 0);
   c->phase.assign(c->g.L, 0);
   c->pending.assign(c->g.L, 0);
+  c->div_parts.assign(c->g.L, 0);
   hipStream_t s = (hipStream_t)hip_stream;
   if (launch_fill_zero(c->kv, c->g.kv_layer_bytes * c->g.L, s) != hipSuccess ||
       launch_fill_zero(c->meta, c->g.meta_layer_bytes * c->g.L, s) != hipSuccess ||
@@ -280,6 +282,7 @@ static int global_attn_impl(ovggt_cache* c, int layer, const void* q, const void
   if (!appends)
     for (int l = l0; l < l0 + nl; ++l) c->pending[l] = 0;
   hipError_t e;
+  int32_t parts = 0;
   if (g.esize == 2) {
     hipEvent_t ev[3] = {nullptr, nullptr, nullptr};
     bool have = false;
@@ -297,8 +300,11 @@ static int global_attn_impl(ovggt_cache* c, int layer, const void* q, const void
                             c->cfg.out_dtype == OVGGT_F32, s);
       if (have && e == hipSuccess) e = hipEventRecord(ev[1], s);
     } else {
+      // the ranking of a frame that will evict starts here, beside the merge pass (never where kernels are timed one by one)
+      const bool rank = g.hybrid && n + g.M > g.B && n > 0 && g.H <= kMergedDivHeads && c->prof_level == 0;
       e = launch_attn_bf16(g, c->kv, l0, nl, q, out, n + g.M, c->scale, ws, ws_bytes, c->n_wgs,
-                           c->cfg.out_dtype == OVGGT_F32, s, have ? ev : nullptr);
+                           c->cfg.out_dtype == OVGGT_F32, s, have ? ev : nullptr, rank ? c->meta : nullptr);
+      if (rank) parts = kDivWavesPerWg * diversity_grid_x(n, nl);
     }
     if (have) {
       c->prof_pending[OVGGT_PROF_ATTN].push_back({ev[0], ev[1]});
@@ -310,7 +316,7 @@ static int global_attn_impl(ovggt_cache* c, int layer, const void* q, const void
     e = launch_attn_f32(g, c->kv, c->meta, l0, nl, q, out, n + g.M, c->scale, ws, ws_bytes, c->n_wgs, s);
   }
   if (e != hipSuccess) return OVGGT_ERR_HIP;
-  for (int l = l0; l < l0 + nl; ++l) { c->n[l] = n + g.M; c->phase[l] = 1; c->pending[l] = 0; }
+  for (int l = l0; l < l0 + nl; ++l) { c->n[l] = n + g.M; c->phase[l] = 1; c->pending[l] = 0; c->div_parts[l] = parts; }
   return OVGGT_OK;
 }
 
@@ -333,9 +339,12 @@ int ovggt_score_select(ovggt_cache* c, int layer, const void* resid, const uint8
   if (!uniform(c, l0, nl, 1)) return OVGGT_ERR_STATE;
   {
     ProfScope ps(c, OVGGT_PROF_SELECT, (hipStream_t)hip_stream, c->prof_level >= 2);
+    int32_t parts = c->div_parts[l0];                // 0 unless every layer's pass has been done, in one launch
+    for (int l = l0; l < l0 + nl; ++l)
+      if (c->div_parts[l] != parts) parts = 0;
     const HybridParams hy = {c->cfg.score_mode == 1 ? 1 : 0, c->cfg.hybrid_beta,
-                             kDivWavesPerWg * diversity_grid_x(c->n[l0] - c->g.M, nl)};
-    if (hy.on && c->n[l0] > c->g.B &&
+                             parts ? parts : kDivWavesPerWg * diversity_grid_x(c->n[l0] - c->g.M, nl)};
+    if (hy.on && c->n[l0] > c->g.B && !parts &&
         launch_diversity(c->g, c->kv, c->meta, l0, nl, c->n[l0] - c->g.M, (hipStream_t)hip_stream) != hipSuccess)
       return OVGGT_ERR_HIP;
     if (launch_score_select(c->g, c->smooth, hy, c->meta, l0, nl, resid, anchor_flags, c->n[l0], (hipStream_t)hip_stream) != hipSuccess)

@@ -106,9 +106,12 @@ bool attn_few_better(const Geom& g, int nl, int n_total, int n_wgs);
 AttnSplit attn_few_split(const Geom& g, int nl, int n_total, size_t ws_bytes, int n_wgs);
 // `ev` (optional, 3 events) are recorded before the main kernel, between it and
 // the combine kernel, and after the combine kernel.
+// diversity_meta (up to kMergedDivHeads heads): the handle's metadata, and the frame's launch_diversity rides along with the
+// combine kernel.
+constexpr int kMergedDivHeads = 16;
 hipError_t launch_attn_bf16(const Geom& g, char* kv, int layer0, int nl, const void* q, void* out,
                             int n_total, float scale, char* ws, size_t ws_bytes, int n_wgs, bool out_f32,
-                            hipStream_t s, hipEvent_t* ev = nullptr);
+                            hipStream_t s, hipEvent_t* ev = nullptr, char* diversity_meta = nullptr);
 size_t attn_ws_bytes(int layer_heads, int query_blocks);
 bool attn_whole_items(int layer_heads, int query_blocks, int n_wgs);
 // The library's own workspace for the attention's partial records (a device array of fixed size, one

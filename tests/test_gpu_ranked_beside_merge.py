@@ -1,0 +1,37 @@
+"""Hybrid scoring where the attention has a merge pass: the diversity pass rides along with it, also when the calls of a frame
+group the layers differently.  Cache bit for bit against the oracle."""
+import numpy as np
+import pytest
+
+from oracle import ovggt_oracle as oc
+from paper_2603_05959_amd import binding as B
+from paper_2603_05959_amd import synth
+from test_gpu_parity import assert_kernel, compare_cache, dev
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("M,H,budget", [(1041, 16, 2400), (1374, 9, 4100), (1374, 5, 8300)])
+def test_layers_grouped_either_way(M, H, budget):
+    import torch
+    cfg = synth.preset(1, M=M, H=H, C=64, B=budget, T=budget // M + 4, n_special=5, L=2)
+    cache = B.Cache(2, H, 64, M, 64, budget, "bf16", hybrid_beta=0.5)
+    assert_kernel(cache, cfg.T - 1, "items")
+    orcs = [oc.OracleCache(M, H, 64, budget, hybrid_beta=0.5) for _ in range(2)]
+    out = cache.new_output()
+    for t in range(cfg.T):
+        fs = [synth.frame_inputs(cfg, l, t) for l in range(2)]
+        q, k, v, r = (dev(np.stack([f[x] for f in fs]), cfg) for x in "qkvr")
+        a = torch.from_numpy(np.stack([f["a"] for f in fs])).cuda()
+        attn_layers = [0, 1] if t % 3 == 1 else [B.OVGGT_ALL_LAYERS]
+        rank_layers = [0, 1] if t % 3 == 2 else [B.OVGGT_ALL_LAYERS]
+        for l in attn_layers:
+            cache.global_attn(*([x if l < 0 else x[l] for x in (q, k, v, out)]), layer=l)
+        for l in rank_layers:
+            cache.score_select(r if l < 0 else r[l], a if l < 0 else a[l], l)
+        cache.compact()
+        for l, o in enumerate(orcs):
+            o.append(fs[l]["k"], fs[l]["v"])
+            o.update(fs[l]["r"], fs[l]["a"])
+            compare_cache(cache, o, layer=l, kv=t == cfg.T - 1)
+    cache.close()
