@@ -230,8 +230,9 @@ def run_workload(cfg, W, K, *, hybrid_beta=None, smooth_alpha=None, rising=False
     # from the committed rocprofv3 summary of this workload (stored-score ranking, no smoothing): HBM
     # bytes per launch, and the kernel's steady-state duration in the trace
     wl = cfg.name.split("-")[0]
-    kernel = {"items": "attn_bf16_kernel", "few": "attn_few_kernel", "f32": "attn_f32_kernel"}[
-        B.ovggt_attn_route(cache.cfg, L, n_keys, torch.cuda.get_device_properties(dev).multi_processor_count)["kernel"]]
+    route = B.ovggt_attn_route(cache.cfg, L, n_keys, torch.cuda.get_device_properties(dev).multi_processor_count)
+    kernel = {"items": "attn_bf16_kernel", "few": "attn_few_kernel",
+              "f32": "attn_f32_small_kernel" if route["rows"] == 16 else "attn_f32_wide_kernel"}[route["kernel"]]
     traffic = profiled_figure("traffic_bytes_per_launch", kernel, wl, L)
     traffic = None if traffic is None else int(traffic)
     trace_us = profiled_figure("trace_avg_kernel_us", kernel, wl, L)
