@@ -265,7 +265,8 @@ int ovggt_cache_last_moves(ovggt_cache* c, int layer, uint32_t* dst, uint32_t* s
 /* Kernel timing for benchmarks (off by default; the hot path records nothing
  * when off).  level 1: bracket the attention kernel of every `every`-th
  * ovggt_global_attn call with HIP events on the call's stream; level 2: bracket
- * every kernel of every call.  ovggt_profile_read synchronises `hip_stream`,
+ * every kernel of every call.  In a bracketed call every kernel is a launch of its own; otherwise the
+ * attention's launches may carry the append or the ranking's first pass.  ovggt_profile_read synchronises `hip_stream`,
  * returns per kernel class the summed elapsed milliseconds and the number of
  * bracketed launches since the last read (host arrays of OVGGT_PROF_CLASSES
  * entries), and resets them. */

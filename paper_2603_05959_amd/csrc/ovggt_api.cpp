@@ -271,9 +271,9 @@ static int global_attn_impl(ovggt_cache* c, int layer, const void* q, const void
   }
   const bool few = g.esize == 2 && attn_few_better(g, nl, n + g.M, c->n_wgs);
   if (all_pending && n != g.B) return OVGGT_ERR_HIP;              // a pending compaction implies a full cache
-  // the attention kernel appends where it can, unless every kernel is timed: then the append is a launch of its own (the
-  // same values either way)
-  const int appends = few && !prof_all && attn_few_appends(g, nl, n + g.M, ws_bytes, c->n_wgs) ? (all_pending ? 2 : 1) : 0;
+  // the attention kernel appends where it can, unless it is timed: then the append is a launch of its own (the same values
+  // either way)
+  const int appends = few && !prof_all && !prof_attn && attn_few_appends(g, nl, n + g.M, ws_bytes, c->n_wgs) ? (all_pending ? 2 : 1) : 0;
   if (!appends) {
     ProfScope ps(c, OVGGT_PROF_APPEND, s, prof_all);
     if (launch_append(g, c->kv, c->meta, l0, nl, k_new, v_new, n, all_pending, s) != hipSuccess)
@@ -300,8 +300,8 @@ static int global_attn_impl(ovggt_cache* c, int layer, const void* q, const void
                             c->cfg.out_dtype == OVGGT_F32, s);
       if (have && e == hipSuccess) e = hipEventRecord(ev[1], s);
     } else {
-      // the ranking of a frame that will evict starts here, beside the merge pass (never where kernels are timed one by one)
-      const bool rank = g.hybrid && n + g.M > g.B && n > 0 && g.H <= kMergedDivHeads && c->prof_level == 0;
+      // the ranking of a frame that will evict starts here, beside the merge pass, unless that is timed
+      const bool rank = g.hybrid && n + g.M > g.B && n > 0 && g.H <= kMergedDivHeads && !prof_all && !prof_attn;
       e = launch_attn_bf16(g, c->kv, l0, nl, q, out, n + g.M, c->scale, ws, ws_bytes, c->n_wgs,
                            c->cfg.out_dtype == OVGGT_F32, s, have ? ev : nullptr, rank ? c->meta : nullptr);
       if (rank) parts = kDivWavesPerWg * diversity_grid_x(n, nl);
